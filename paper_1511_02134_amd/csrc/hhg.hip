@@ -16,6 +16,7 @@
 #include "hierarchy.hpp"
 #include "kernels.hpp"
 #include "krylov.hpp"
+#include "lattice.hpp"
 
 using namespace hhg;
 
@@ -51,6 +52,10 @@ thread_local std::string g_error;
 
 // leading interface blocks of a launch: ceil(count / TPB), padded to a multiple of 8
 inline int iface_blocks(int count) { return ((count + TPB - 1) / TPB + 7) / 8 * 8; }
+
+// surface blocks of a lattice launch with bs lanes each, a multiple of 8 (the
+// volume tiles keep their XCD)
+inline int lat_sblocks(const LatSurf& B, int bs) { return ((B.beg[6] + bs - 1) / bs + 7) / 8 * 8; }
 
 struct Carver {
     char* base;
@@ -89,6 +94,18 @@ struct DevLevelArrays {
     float* snap32;
 };
 
+// Lattice path (lattice.hpp) of one level: device tables and work vectors
+// (4 fields each; the FP64 ones below the finest level only without mixed
+// precision, whose cycles run in FP32)
+struct LatLevel {
+    int* rid = nullptr;
+    unsigned char* rdir = nullptr;
+    double *rec64 = nullptr, *axr64 = nullptr, *x64 = nullptr, *b64 = nullptr, *r64 = nullptr;
+    float *rec32 = nullptr, *axr32 = nullptr, *x32 = nullptr, *b32 = nullptr, *r32 = nullptr;
+    int nrec = 0, nrid = 0;
+    LatSurf svel, spres, sfull;   // surface lanes of velocity, pressure and full launches
+};
+
 constexpr int KV_N = 10;   // finest-level vectors of the Krylov solvers
 
 struct TimerPair {
@@ -112,6 +129,14 @@ struct hhg_ctx {
     std::vector<LevelDev<double>> D64;
     std::vector<LevelDev<float>> D32;
     CoarseDev cd{};
+    // lattice path: the cycles run on the structured lattice (lattice.hpp)
+    bool lat = false;
+    int lat_kind = 0;              // 0: one viscosity, 1: per-macro viscosities
+    std::vector<LatLevel> G;
+    std::vector<Lat<double>> G64;
+    std::vector<Lat<float>> G32;
+    CoarseDev cdl{};               // cd with the level-0 tables of the lattice layout
+    double lbytes_vel[4] = {0, 0, 0, 0};   // algorithmic bytes of a velocity colour launch
     size_t coarse_smem = 0;
     double* partials = nullptr;
     int npartials = 0;
@@ -233,6 +258,59 @@ bool build_coarse_for(hhg_ctx* c, std::string* err) {
     return build_coarse(c->mi, c->H[0], direct, schur, c->opts.op == 1, &c->CH, err);
 }
 
+// geometry of a level's lattice (sizes and strides; no tables)
+template <typename T>
+Lat<T> lat_geometry(const hhg_ctx* c, int l) {
+    const HostLevel& h = c->H[l];
+    Lat<T> G{};
+    G.nx = h.lat[0];
+    G.ny = h.lat[1];
+    G.nz = h.lat[2];
+    G.n = h.n;
+    G.sh = h.R;
+    G.Qi = (G.nx - 1) / 4;
+    G.Qp = (G.Qi + 2) / 2 * 2;
+    G.RS = 4 * G.Qp;
+    G.ZS = G.RS * G.ny;
+    G.cx = c->mi.ext[0];
+    G.cy = c->mi.ext[1];
+    G.order = c->opts.block_order;
+    G.len = ((size_t)G.ZS * G.nz + 63) / 64 * 64;
+    return G;
+}
+
+// The workspace holds the lattice path's tables and vectors for Kuhn macros
+// without free-slip faces and at least one smoothed level.  The limits are
+// those of its 32-bit addresses and of lat_div.
+bool lat_reserved(const hhg_ctx* c) {
+    if (c->mi.general || c->mi.slip || c->L < 1) return false;
+    const HostLevel& h = c->H[c->L];
+    const int64_t lim = 1 << 21, plane = (int64_t)h.lat[0] * h.lat[1];
+    const Lat<double> G = lat_geometry<double>(c, c->L);
+    const int64_t tiles = ((int64_t)h.lat[1] * G.Qi / 256 + 1) * h.lat[2];
+    return plane < lim && tiles < lim && (int64_t)G.RS * G.ny * G.nz < (1LL << 29) - 64 && h.lat[2] < 65536;
+}
+
+// Lanes per workgroup: levels with fewer than 2048 full waves of work spread
+// them one wave to a workgroup over the CUs (a launch there waits on the loads
+// of its slowest workgroup), larger ones take 256 lanes.
+template <typename T>
+int lat_bs(const Lat<T>& G) {
+    return (int64_t)lat_quad_lanes(G) * G.nz < 2048 * 64 ? 64 : 256;
+}
+
+// It runs the Laplace form in the colour and the red-black order.
+bool lat_applies(const hhg_ctx* c) {
+    return lat_reserved(c) && c->opts.op == 0 && c->opts.ordering != 1;
+}
+
+LatSurf lat_surface(const Lat<double>& G, int S, int faces) {
+    LatSurf B;
+    B.beg[0] = 0;
+    for (int f = 0; f < 6; ++f) B.beg[f + 1] = B.beg[f] + (faces >> f & 1 ? lat_face_lanes(G, f, S) : 0);
+    return B;
+}
+
 // Builds the host hierarchy and computes the workspace layout (when ws is
 // NULL only the size).
 hhg_status build_host(hhg_ctx* c, const hhg_mesh* mesh, int R, const hhg_opts* opts) {
@@ -265,6 +343,7 @@ hhg_status build_host(hhg_ctx* c, const hhg_mesh* mesh, int R, const hhg_opts* o
             if (t < 0) return fail(c, HHG_EINVAL, "internal error: coarse interface vertex missing");
     }
     if (!build_coarse_for(c, &err)) return fail(c, HHG_EINVAL, err);
+    c->lat = lat_applies(c);
     return HHG_OK;
 }
 
@@ -342,6 +421,53 @@ size_t layout(hhg_ctx* c, char* ws) {
         maxblocks = std::max(maxblocks, nb);
         maxblocks = std::max(maxblocks, (int)h.ctiles.size());
     }
+    const bool lat = lat_reserved(c);
+    c->G.assign(lat ? nl : 0, LatLevel{});
+    if (lat) {
+        // faces of the box (z0, z1, y0, y1, x0, x1) with a vertex that is not
+        // Dirichlet, from the level-0 lattice (every level has the same)
+        int vel_faces = 0;
+        {
+            const HostLevel& h = c->H[0];
+            for (int64_t v = 0; v < h.N; ++v) {
+                if (h.node_dir[v]) continue;
+                const int X = (int)(v % h.lat[0]), Y = (int)(v / h.lat[0] % h.lat[1]),
+                          Z = (int)(v / ((int64_t)h.lat[0] * h.lat[1]));
+                vel_faces |= (Z == 0 ? 1 : 0) | (Z == h.lat[2] - 1 ? 2 : 0) | (Y == 0 ? 4 : 0) |
+                             (Y == h.lat[1] - 1 ? 8 : 0) | (X == 0 ? 16 : 0) | (X == h.lat[0] - 1 ? 32 : 0);
+            }
+        }
+        for (int l = 0; l < nl; ++l) {
+            LatLevel& g = c->G[l];
+            const Lat<double> G = lat_geometry<double>(c, l);
+            const int S = c->opts.ordering == 2 ? 2 : 4;
+            g.svel = lat_surface(G, S, vel_faces);
+            g.spres = lat_surface(G, S, 63);
+            g.sfull = lat_surface(G, 1, 63);
+            g.nrec = c->H[l].nm + (int)c->H[l].keys.size();
+            g.nrid = (c->mi.ext[0] + 1) * (c->mi.ext[1] + 1) * (c->mi.ext[2] + 1) * LPAT;
+            g.rid = cv.take<int>(g.nrid);
+            g.rdir = cv.take<unsigned char>(g.nrec);
+            g.rec64 = cv.take<double>((size_t)g.nrec * LR_SIZE);
+            g.axr64 = cv.take<double>((size_t)g.nrec * LX_SIZE);
+            const size_t v4 = 4 * G.len;
+            if (!mixed || l == c->L) {
+                g.x64 = cv.take<double>(v4);
+                g.b64 = cv.take<double>(v4);
+                g.r64 = cv.take<double>(v4);
+            }
+            if (mixed) {
+                g.rec32 = cv.take<float>((size_t)g.nrec * LR_SIZE);
+                g.axr32 = cv.take<float>((size_t)g.nrec * LX_SIZE);
+                g.x32 = cv.take<float>(v4);
+                g.b32 = cv.take<float>(v4);
+                g.r32 = cv.take<float>(v4);
+            }
+            maxblocks = std::max(maxblocks, lat_grid(lat_quad_lanes(G), G.nz - 2, lat_bs(G)).total +
+                                                lat_sblocks(g.sfull, lat_bs(G)));
+            maxblocks = std::max(maxblocks, ((G.Qi + 1) * G.ny + 255) / 256 * G.nz);
+        }
+    }
     c->npartials = maxblocks;
     c->partials = cv.take<double>(maxblocks);
     c->gpart = cv.take<double>(maxblocks);
@@ -367,6 +493,8 @@ size_t layout(hhg_ctx* c, char* ws) {
     d.node_cptr = cv.take<int32_t>(C.node_cptr.size());
     d.node_copy = cv.take<int32_t>(C.node_copy.size());
     d.gscratch = cv.take<double>((size_t)8 * C.nd);
+    int32_t* lslot = lat ? cv.take<int32_t>(C.N) : nullptr;
+    int32_t* lcptr = lat ? cv.take<int32_t>(C.N + 1) : nullptr;
     // direct solver: the bordered matrix, inverted in place at set-up, its
     // column permutation, the elimination factors and the pivot state
     d.nb = C.nb;
@@ -376,6 +504,8 @@ size_t layout(hhg_ctx* c, char* ws) {
     c->gj_state = cv.take<GJState>(1);
     d.a2inv = cv.take<double>(std::max<size_t>(1, C.a2inv.size()));
     d.coupled = C.a2inv.empty() ? 0 : 1;
+    c->cdl.node_slot = c->cdl.node_copy = lslot;
+    c->cdl.node_cptr = lcptr;
     return cv.off + 256;
 }
 
@@ -454,6 +584,105 @@ hhg_status coarse_direct_setup(hhg_ctx* c) {
     return HHG_OK;
 }
 
+// Records and constants of the lattice path (with every change of viscosity).
+hhg_status upload_lattice(hhg_ctx* c) {
+    if (!c->lat) return HHG_OK;
+    c->lat_kind = 0;
+    for (const MacroInfo& m : c->mi.macros)
+        if (m.nu != c->mi.macros[0].nu) c->lat_kind = 1;
+    c->G64.assign(c->L + 1, Lat<double>{});
+    c->G32.assign(c->L + 1, Lat<float>{});
+    for (int l = 0; l <= c->L; ++l) {
+        const HostLevel& h = c->H[l];
+        LatLevel& g = c->G[l];
+        Lat<double> G = lat_geometry<double>(c, l);
+        std::vector<double> rec((size_t)g.nrec * LR_SIZE, 0.0), axr((size_t)g.nrec * LX_SIZE, 0.0);
+        std::vector<unsigned char> dir(g.nrec, 0);
+        std::vector<int> rid(g.nrid, 0);
+        for (int r = 0; r < g.nrec; ++r) {
+            const double* st = r < h.nm ? &h.st_vol_global[(size_t)r * ST_SIZE] : &h.st[(size_t)r * ST_SIZE];
+            double* o = &rec[(size_t)r * LR_SIZE];
+            for (int q = 0; q < 15; ++q) {
+                o[LR_A + q] = st[ST_A + q];
+                o[LR_C + q] = st[ST_C + q];
+                for (int k = 0; k < 3; ++k) {
+                    o[LR_B + 15 * k + q] = st[ST_B + 15 * k + q];
+                    o[LR_BT + 15 * k + q] = st[ST_BT + 15 * k + q];
+                }
+            }
+            o[LR_INVA] = st[ST_INVA];
+            o[LR_INVC] = st[ST_INVC];
+            o[LR_MASS] = st[ST_MASS];
+            double* a = &axr[(size_t)r * LX_SIZE];
+            for (int q = 0; q < 6; ++q) {
+                a[LX_A + q] = st[ST_A + 1 + q];
+                a[LX_C + q] = st[ST_C + 1 + q];
+            }
+            a[LX_A0] = st[ST_A];
+            a[LX_INVA] = st[ST_INVA];
+            a[LX_C0] = st[ST_C];
+            a[LX_INVC] = st[ST_INVC];
+        }
+        // the vertices with offsets 0..3 in every cell show each pattern
+        const int n = h.n;
+        for (int Z = 0; Z < G.nz; ++Z)
+            for (int Y = 0; Y < G.ny; ++Y)
+                for (int X = 0; X < G.nx; ++X) {
+                    if ((X & (n - 1)) > 3 || (Y & (n - 1)) > 3 || (Z & (n - 1)) > 3) continue;
+                    const int64_t v = X + (int64_t)G.nx * (Y + (int64_t)G.ny * Z);
+                    const int sid = h.node_sid[v] < 0 ? -h.node_sid[v] - 1 : h.node_sid[v];
+                    rid[lat_rid_index(G, X, Y, Z)] = sid;
+                    if (h.node_dir[v]) dir[sid] = 1;
+                }
+        // constants of the interior vertices (pair symmetries as in the
+        // volume records)
+        const double* st = &h.st_vol_global[0];
+        for (int q = 0; q < 3; ++q) {
+            G.a[q] = 0.5 * (st[ST_A + 2 * q + 1] + st[ST_A + 2 * q + 2]);
+            G.c[q] = 0.5 * (st[ST_C + 2 * q + 1] + st[ST_C + 2 * q + 2]);
+        }
+        G.a0 = st[ST_A];
+        G.inva = st[ST_INVA];
+        G.c0 = st[ST_C];
+        G.invc = st[ST_INVC];
+        G.mass = st[ST_MASS];
+        for (int k = 0; k < 3; ++k)
+            for (int q = 0; q < 7; ++q)
+                G.bt[k][q] = 0.25 * (st[ST_BT + 15 * k + 2 * q + 1] - st[ST_BT + 15 * k + 2 * q + 2] -
+                                     st[ST_B + 15 * k + 2 * q + 1] + st[ST_B + 15 * k + 2 * q + 2]);
+        hhg_status s;
+        if ((s = upload<int>(c, g.rid, rid.data(), rid.size())) != HHG_OK) return s;
+        if ((s = upload<unsigned char>(c, g.rdir, dir.data(), dir.size())) != HHG_OK) return s;
+        if ((s = upload<double>(c, g.rec64, rec.data(), rec.size())) != HHG_OK) return s;
+        if ((s = upload<double>(c, g.axr64, axr.data(), axr.size())) != HHG_OK) return s;
+        Lat<float> F = lat_geometry<float>(c, l);
+        for (int q = 0; q < 3; ++q) {
+            F.a[q] = (float)G.a[q];
+            F.c[q] = (float)G.c[q];
+            for (int p = 0; p < 7; ++p) F.bt[q][p] = (float)G.bt[q][p];
+        }
+        F.a0 = (float)G.a0;
+        F.inva = (float)G.inva;
+        F.c0 = (float)G.c0;
+        F.invc = (float)G.invc;
+        F.mass = (float)G.mass;
+        G.rid = F.rid = g.rid;
+        G.rdir = F.rdir = g.rdir;
+        G.rec = g.rec64;
+        G.axr = g.axr64;
+        F.rec = g.rec32;
+        F.axr = g.axr32;
+        if (g.rec32) {
+            std::vector<float> r32(rec.begin(), rec.end()), a32(axr.begin(), axr.end());
+            if ((s = upload<float>(c, g.rec32, r32.data(), r32.size())) != HHG_OK) return s;
+            if ((s = upload<float>(c, g.axr32, a32.data(), a32.size())) != HHG_OK) return s;
+        }
+        c->G64[l] = G;
+        c->G32[l] = F;
+    }
+    return HHG_OK;
+}
+
 hhg_status upload_stencils(hhg_ctx* c) {
     for (int l = 0; l <= c->L; ++l) {
         HostLevel& h = c->H[l];
@@ -501,6 +730,25 @@ hhg_status upload_stencils(hhg_ctx* c) {
     if ((s = upload<double>(c, (double*)c->cd.mass, C.mass.data(), C.mass.size())) != HHG_OK)
         return s;
     c->cd.inv_mass = c->inv_mass[0];
+    if (c->lat) {
+        // the level-0 tables in the lattice layout: one copy per vertex
+        const Lat<double> G = lat_geometry<double>(c, 0);
+        std::vector<int32_t> slot(C.N), cptr(C.N + 1);
+        for (int v = 0; v < C.N; ++v) {
+            const int nd = C.node_lat[v];
+            slot[v] = lat_at(G, nd % G.nx, nd / G.nx % G.ny, nd / (G.nx * G.ny));
+            cptr[v] = v;
+        }
+        cptr[C.N] = C.N;
+        CoarseDev d = c->cd;
+        d.node_slot = c->cdl.node_slot;
+        d.node_copy = c->cdl.node_copy;
+        d.node_cptr = c->cdl.node_cptr;
+        c->cdl = d;
+        if ((s = upload<int32_t>(c, (int32_t*)d.node_slot, slot.data(), slot.size())) != HHG_OK) return s;
+        if ((s = upload<int32_t>(c, (int32_t*)d.node_cptr, cptr.data(), cptr.size())) != HHG_OK) return s;
+        if ((s = upload_lattice(c)) != HHG_OK) return s;
+    }
     {
         // pressure preconditioner of the Krylov solvers on the finest level:
         // 1 / (lumped pressure mass weighted by 1/nu) on every copy; it
@@ -651,6 +899,8 @@ hhg_status upload_all(hhg_ctx* c) {
         // the D form's velocity sweep reads the neighbours of every other colour
         const double vnbr = dpath(c) ? Nall - Nc[col] : nbr;   // 15-tap rows read every other colour
         c->bytes_vel[col] = vs * 3.0 * (vnbr + 2.0 * Nfc[col]);
+        // the lattice path's sweep reads p too (its rows of B^T p)
+        c->lbytes_vel[col] = c->bytes_vel[col] + vs * Nall * (c->opts.ordering == 2 ? 0.5 : 1.0);
         c->bytes_pres[col] = vs * ((c->mi.general ? Nall - Nc[col] : nbr) + 3.0 * Nc[col]);
     }
     c->bytes_ru = vs * (Nall + 6.0 * Nf);
@@ -1333,18 +1583,22 @@ void prolong_add(hhg_ctx* c, int l, const T* ec, T* xf, hipStream_t s) {
                            0, s, F, C, ec, xf);
 }
 
+// cd: the level-0 tables of the layout of b and x (fields of stride len)
 template <typename T>
-void coarse_solve(hhg_ctx* c, const T* b, T* x, hipStream_t s) {
-    const size_t len = (size_t)c->H[0].len;
+void coarse_solve(hhg_ctx* c, const T* b, T* x, hipStream_t s, const CoarseDev& cd, size_t len) {
     if (c->opts.coarse_solver == 0) {
-        const int rows = (c->cd.nd + TPB / 64 - 1) / (TPB / 64);
-        const int grid = std::max(rows, (c->cd.N + TPB - 1) / TPB);
-        hipLaunchKernelGGL(k_coarse_direct<T>, dim3(grid), dim3(TPB), c->cd.nb * sizeof(double), s,
-                           c->cd, b, len, x, len, c->scal + 8);
+        const int rows = (cd.nd + TPB / 64 - 1) / (TPB / 64);
+        const int grid = std::max(rows, (cd.N + TPB - 1) / TPB);
+        hipLaunchKernelGGL(k_coarse_direct<T>, dim3(grid), dim3(TPB), cd.nb * sizeof(double), s, cd, b,
+                           len, x, len, c->scal + 8);
         return;
     }
-    hipLaunchKernelGGL(k_coarse<T>, dim3(1), dim3(CTPB), c->coarse_smem, s, c->cd, b, len, x, len,
+    hipLaunchKernelGGL(k_coarse<T>, dim3(1), dim3(CTPB), c->coarse_smem, s, cd, b, len, x, len,
                        c->scal + 8);
+}
+template <typename T>
+void coarse_solve(hhg_ctx* c, const T* b, T* x, hipStream_t s) {
+    coarse_solve<T>(c, b, x, s, c->cd, (size_t)c->H[0].len);
 }
 
 template <typename T>
@@ -1414,6 +1668,217 @@ void vcycle(hhg_ctx* c, int l, int top, T* x, const T* b, hipStream_t s,
     }
     PhaseTimed pt(c, PH_SMOOTH, l, s);
     for (int q = 0; q < c->opts.nu2 + extra; ++q) uzawa_step<T>(c, l, x, b, tl, s);
+}
+
+// ------------------------------------------------------- lattice path
+template <typename T>
+struct LatVecs {
+    const Lat<T>& G;
+    const LatLevel& g;
+    T *x, *b, *r;
+};
+template <typename T>
+LatVecs<T> lat_vecs(hhg_ctx* c, int l);
+template <>
+LatVecs<double> lat_vecs<double>(hhg_ctx* c, int l) {
+    return {c->G64[l], c->G[l], c->G[l].x64, c->G[l].b64, c->G[l].r64};
+}
+template <>
+LatVecs<float> lat_vecs<float>(hhg_ctx* c, int l) {
+    return {c->G32[l], c->G[l], c->G[l].x32, c->G[l].b32, c->G[l].r32};
+}
+
+
+// velocity sweep of parity (ordering 2) or colour col
+template <typename T>
+void lat_vel(hhg_ctx* c, int l, int col, bool pz, int cls, T* x, const T* b, hipStream_t s) {
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    const bool rb = c->opts.ordering == 2;
+    const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.nz - 2, lat_bs(v.G));
+    const int sb = lat_sblocks(v.g.svel, tg.bs);
+    const dim3 grid(sb + tg.total), blk(tg.bs);
+    ops(c, l, rb ? 0.5 : 0.25, 0, 0, 0);
+    Timed tm(c, cls, s, l == c->L, rb ? c->lbytes_vel[col] + c->lbytes_vel[col + 2] : c->lbytes_vel[col]);
+#define LAT_VEL(K, NC, PZ) \
+    hipLaunchKernelGGL((k_lat_vel<T, K, NC, PZ>), grid, blk, 0, s, v.G, v.g.svel, col, sb, tg, b, x)
+    const int sel = (c->lat_kind ? 4 : 0) + (rb ? 2 : 0) + (pz ? 1 : 0);
+    switch (sel) {
+        case 0: LAT_VEL(0, 1, false); break;
+        case 1: LAT_VEL(0, 1, true); break;
+        case 2: LAT_VEL(0, 2, false); break;
+        case 3: LAT_VEL(0, 2, true); break;
+        case 4: LAT_VEL(1, 1, false); break;
+        case 5: LAT_VEL(1, 1, true); break;
+        case 6: LAT_VEL(1, 2, false); break;
+        default: LAT_VEL(1, 2, true); break;
+    }
+#undef LAT_VEL
+}
+
+template <typename T>
+void lat_pres(hhg_ctx* c, int l, int col, T* x, const T* sx, hipStream_t s) {
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    const bool rb = c->opts.ordering == 2;
+    const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.nz - 2, lat_bs(v.G));
+    const int sb = lat_sblocks(v.g.spres, tg.bs);
+    const dim3 grid(sb + tg.total), blk(tg.bs);
+    T* p = x + 3 * v.G.len;
+    const T om = (T)c->opts.omega;
+    ops(c, l, 0, 0, rb ? 0.5 : 0.25, 0);
+    Timed tm(c, HHG_K_PRES, s, l == c->L, rb ? c->bytes_pres[col] + c->bytes_pres[col + 2] : c->bytes_pres[col]);
+    if (c->lat_kind == 0 && rb)
+        hipLaunchKernelGGL((k_lat_pres<T, 0, 2>), grid, blk, 0, s, v.G, v.g.spres, col, sb, tg, sx, p, om);
+    else if (c->lat_kind == 0)
+        hipLaunchKernelGGL((k_lat_pres<T, 0, 1>), grid, blk, 0, s, v.G, v.g.spres, col, sb, tg, sx, p, om);
+    else if (rb)
+        hipLaunchKernelGGL((k_lat_pres<T, 1, 2>), grid, blk, 0, s, v.G, v.g.spres, col, sb, tg, sx, p, om);
+    else
+        hipLaunchKernelGGL((k_lat_pres<T, 1, 1>), grid, blk, 0, s, v.G, v.g.spres, col, sb, tg, sx, p, om);
+}
+
+// B u - g with the first pressure sweep (red or colour 0)
+template <typename T>
+void lat_bp(hhg_ctx* c, int l, T* x, const T* b, T* sx, hipStream_t s) {
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    const bool rb = c->opts.ordering == 2;
+    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.nz - 2, lat_bs(v.G));
+    const int sb = lat_sblocks(v.g.sfull, tg.bs);
+    const dim3 grid(sb + tg.total), blk(tg.bs);
+    const T om = (T)c->opts.omega;
+    const int all = c->opts.p_sweep;
+    ops(c, l, 0, 1, rb ? 0.5 : 0.25, 0);
+    Timed tm(c, HHG_K_APPLY, s, l == c->L, c->bytes_bp_fused[rb ? 4 : 0]);
+    if (c->lat_kind == 0 && rb)
+        hipLaunchKernelGGL((k_lat_bp<T, 0, 2>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+    else if (c->lat_kind == 0)
+        hipLaunchKernelGGL((k_lat_bp<T, 0, 1>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+    else if (rb)
+        hipLaunchKernelGGL((k_lat_bp<T, 1, 2>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+    else
+        hipLaunchKernelGGL((k_lat_bp<T, 1, 1>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+}
+
+// One inexact Uzawa step (the steps of uzawa_step and uzawa_step_rb).  pz: the
+// pressure of x is 0; given: f - B^T p of this x counts as evaluated (by the
+// stopping test's residual, or x = 0)
+template <typename T>
+void lat_uzawa(hhg_ctx* c, int l, T* x, const T* b, T* r, hipStream_t s, bool pz, bool given) {
+    const bool rb = c->opts.ordering == 2;
+    static const int rorder[3] = {0, 1, 0}, corder[7] = {0, 1, 2, 3, 2, 1, 0};
+    const int nv = rb ? 3 : 7;
+    const int* order = rb ? rorder : corder;
+    if (!given) {
+        ops(c, l, 0, 1, 0, 0);
+        lat_vel<T>(c, l, order[0], pz, HHG_K_RU, x, b, s);
+    }
+    {
+        TimedGroup tg(c, HHG_K_VEL, s, l == c->L);
+        for (int q = given ? 0 : 1; q < nv; ++q) lat_vel<T>(c, l, order[q], pz, HHG_K_VEL, x, b, s);
+    }
+    T* sx = r + 3 * lat_vecs<T>(c, l).G.len;
+    lat_bp<T>(c, l, x, b, sx, s);
+    const int nc = rb ? 2 : 4;
+    for (int col = 1; col < nc; ++col) lat_pres<T>(c, l, col, x, sx, s);
+    if (c->opts.p_sweep == 1)
+        for (int col = nc - 1; col >= 0; --col) lat_pres<T>(c, l, col, x, sx, s);
+}
+
+// r = b - K x on level l; out: its norm; r NULL: the norm alone
+template <typename T>
+void lat_residual(hhg_ctx* c, int l, const T* x, const T* b, T* r, double* out, hipStream_t s) {
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.nz - 2, lat_bs(v.G));
+    const int sb = lat_sblocks(v.g.sfull, tg.bs);
+    const dim3 grid(sb + tg.total), blk(tg.bs);
+    ops(c, l, 1, 2, 1, 0);
+    {
+        Timed tm(c, HHG_K_APPLY, s, l == c->L, c->bytes_res);
+#define LAT_RES(K, WR, NRM) \
+    hipLaunchKernelGGL((k_lat_res<T, K, WR, NRM>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg, b, x, r, c->partials)
+        if (!out) {
+            if (c->lat_kind) LAT_RES(1, true, false);
+            else LAT_RES(0, true, false);
+        } else if (r) {
+            if (c->lat_kind) LAT_RES(1, true, true);
+            else LAT_RES(0, true, true);
+        } else {
+            if (c->lat_kind) LAT_RES(1, false, true);
+            else LAT_RES(0, false, true);
+        }
+#undef LAT_RES
+    }
+    if (out)
+        hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(RTPB), 0, s, c->partials,
+                           tg.total + (v.g.sfull.beg[6] + tg.bs - 1) / tg.bs, out, 1);
+}
+
+template <typename T>
+void lat_project(hhg_ctx* c, int l, T* x, hipStream_t s) {
+    if (!c->mi.project) return;
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    T* p = x + 3 * v.G.len;
+    const dim3 grid(((v.G.Qi + 1) * v.G.ny + 255) / 256, v.G.nz);
+    hipLaunchKernelGGL(k_lat_mass<T>, grid, dim3(256), 0, s, v.G, (const T*)p, c->partials);
+    hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(RTPB), 0, s, c->partials, (int)(grid.x * grid.y),
+                       c->scal + 4, 0);
+    hipLaunchKernelGGL(k_sub_mean<T>, dim3(grid_for(v.G.len)), dim3(TPB), 0, s, p, v.G.len, c->scal + 4,
+                       c->inv_mass[l]);
+}
+
+template <typename T, bool SET>
+void lat_prolong(hhg_ctx* c, int l, const T* ec, T* xf, hipStream_t s) {
+    const LatVecs<T> f = lat_vecs<T>(c, l), v = lat_vecs<T>(c, l - 1);
+    hipLaunchKernelGGL((k_lat_prolong<T, SET>), dim3(((f.G.Qi + 1) * f.G.ny + 255) / 256, f.G.nz), dim3(256), 0,
+                       s, f.G, v.G, ec, xf);
+}
+
+// vcycle on the lattice path (l >= 1).  zero: x = 0 on entry; given: as in
+// lat_uzawa, for the first step
+template <typename T>
+void lat_vcycle(hhg_ctx* c, int l, int top, T* x, const T* b, hipStream_t s, bool zero, bool given) {
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    const int extra = c->opts.cycle == 1 ? 2 * (top - l) : 0;
+    {
+        PhaseTimed pt(c, PH_SMOOTH, l, s);
+        for (int q = 0; q < c->opts.nu1 + extra; ++q)
+            lat_uzawa<T>(c, l, x, b, v.r, s, zero && q == 0, given && q == 0);
+    }
+    {
+        PhaseTimed pt(c, PH_RESIDUAL, l, s);
+        lat_residual<T>(c, l, x, b, v.r, nullptr, s);
+    }
+    const LatVecs<T> w = lat_vecs<T>(c, l - 1);
+    {
+        PhaseTimed pt(c, PH_TRANSFER, l, s);
+        const LatGrid tg = lat_grid(lat_quad_lanes(w.G), w.G.nz - 2, lat_bs(w.G));
+        const int sb = lat_sblocks(w.g.sfull, tg.bs);
+        hipLaunchKernelGGL(k_lat_restrict<T>, dim3(sb + tg.total), dim3(tg.bs), 0, s, w.G, v.G,
+                           w.g.sfull, sb, tg, (const T*)v.r, w.b, w.x);
+    }
+    if (l == 1) {
+        PhaseTimed pt(c, PH_COARSE, 0, s);
+        coarse_solve<T>(c, w.b, w.x, s, c->cdl, w.G.len);
+    } else {
+        lat_vcycle<T>(c, l - 1, top, w.x, w.b, s, true, true);
+    }
+    {
+        PhaseTimed pt(c, PH_TRANSFER, l, s);
+        lat_prolong<T, false>(c, l, w.x, x, s);
+    }
+    PhaseTimed pt(c, PH_SMOOTH, l, s);
+    for (int q = 0; q < c->opts.nu2 + extra; ++q) lat_uzawa<T>(c, l, x, b, v.r, s, false, false);
+}
+
+// conversions between a caller's vector and the lattice layout
+void lat_in(hhg_ctx* c, int l, const double* v, double* x, hipStream_t s) {
+    const Lat<double>& G = c->G64[l];
+    hipLaunchKernelGGL(k_lat_in<double>, dim3((G.nx * G.ny + 255) / 256, G.nz), dim3(256), 0, s, G,
+                       c->A[l].node_slot, v, (size_t)c->H[l].len, x);
+}
+void lat_out(hhg_ctx* c, int l, const double* x, double* v, hipStream_t s) {
+    const size_t len = (size_t)c->H[l].len;
+    hipLaunchKernelGGL(k_lat_out<double>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, c->G64[l],
+                       c->A[l].slot_node, len, x, v);
 }
 
 // ------------------------------------------------------- velocity multigrid
@@ -1866,12 +2331,28 @@ namespace {
 // r64_L must hold b - K x and scal[0] its norm, of the FP64 one with t_ready
 // t64_L f - B^T p
 void cycle_fp64(hhg_ctx* c, double* x, const double* b, hipStream_t s, bool t_ready = false) {
+    if (c->lat) {   // x and b in the lattice layout
+        lat_vcycle<double>(c, c->L, c->L, x, b, s, false, t_ready);
+        lat_project<double>(c, c->L, x, s);
+        return;
+    }
     vcycle<double>(c, c->L, c->L, x, b, s, t_ready ? c->A[c->L].t64 : nullptr);
     project<double>(c, c->L, x, s);
 }
 
 void cycle_mixed(hhg_ctx* c, double* x, hipStream_t s) {
     const int L = c->L;
+    if (c->lat) {   // x in the lattice layout
+        const LatVecs<float> v = lat_vecs<float>(c, L);
+        const size_t n4 = 4 * v.G.len;
+        hipLaunchKernelGGL(k_scale_cast<float>, dim3(grid_for(n4)), dim3(TPB), 0, s, c->G[L].r64, c->scal,
+                           v.b, n4);
+        fill<float>(v.x, n4, 0.f, s);
+        lat_vcycle<float>(c, L, L, v.x, v.b, s, true, true);
+        hipLaunchKernelGGL(k_axpy_cast<float>, dim3(grid_for(n4)), dim3(TPB), 0, s, x, c->scal, v.x, n4);
+        lat_project<double>(c, L, x, s);
+        return;
+    }
     DevLevelArrays& a = c->A[L];
     const size_t n4 = 4 * (size_t)c->H[L].len;
     hipLaunchKernelGGL(k_scale_cast<float>, dim3(grid_for(n4)), dim3(TPB), 0, s, a.r64, c->scal,
@@ -1894,7 +2375,18 @@ hhg_status hhg_vcycle(hhg_ctx* c, void* x, const void* b, hhg_stream stream) {
     CHECK_PTR(c, b);
     if (x == b) return fail(c, HHG_EINVAL, "x and b must not alias");
     hipStream_t s = (hipStream_t)stream;
-    if (c->opts.precision == 1) {
+    if (c->lat) {
+        const LatLevel& g = c->G[c->L];
+        lat_in(c, c->L, (const double*)x, g.x64, s);
+        lat_in(c, c->L, (const double*)b, g.b64, s);
+        if (c->opts.precision == 1) {
+            lat_residual<double>(c, c->L, g.x64, g.b64, g.r64, c->scal, s);
+            cycle_mixed(c, g.x64, s);
+        } else {
+            cycle_fp64(c, g.x64, g.b64, s);
+        }
+        lat_out(c, c->L, g.x64, (double*)x, s);
+    } else if (c->opts.precision == 1) {
         residual_norm<double>(c, c->L, (const double*)x, (const double*)b, c->A[c->L].r64, c->scal, s);
         cycle_mixed(c, (double*)x, s);
     } else {
@@ -1926,6 +2418,23 @@ hhg_status hhg_fmg(hhg_ctx* c, void* const* xs, const void* const* bs, int32_t c
                            (double*)xs[0]);
         vcycle<double>(c, 0, 0, (double*)xs[0], (const double*)bs[0], s);
         project<double>(c, 0, (double*)xs[0], s);
+    }
+    if (c->lat) {
+        // level by level on the lattice, each iterate written back when done
+        lat_in(c, 0, (const double*)xs[0], c->G[0].x64, s);
+        for (int l = 1; l <= c->L; ++l) {
+            const LatLevel& g = c->G[l];
+            lat_in(c, l, (const double*)xs[l], g.x64, s);
+            lat_in(c, l, (const double*)bs[l], g.b64, s);
+            lat_prolong<double, true>(c, l, c->G[l - 1].x64, g.x64, s);
+            for (int q = 0; q < cycles; ++q) {
+                lat_vcycle<double>(c, l, l, g.x64, g.b64, s, false, false);
+                lat_project<double>(c, l, g.x64, s);
+            }
+            lat_out(c, l, g.x64, (double*)xs[l], s);
+        }
+        LAUNCH_CHECK(c);
+        return HHG_OK;
     }
     for (int l = 1; l <= c->L; ++l) {
         LevelDev<double>& F = view<double>(c, l);
@@ -1971,9 +2480,21 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
     // stopping test also leaves f - B^T p of x in t for the next cycle's
     // first Uzawa step.
     const bool fp64 = c->opts.precision != 1;
-    const bool tfuse = fp64 && !dpath(c) && c->opts.ordering != 1;
+    const bool tfuse = fp64 && !c->lat && !dpath(c) && c->opts.ordering != 1;
     double* tL = c->A[c->L].t64;
-    if (tfuse) {
+    // lattice path: the cycles run on x and b converted once; x is written
+    // back on every exit
+    double* xs = x;
+    const double* bs = b;
+    if (c->lat) {
+        const LatLevel& g = c->G[c->L];
+        lat_in(c, c->L, x, g.x64, s);
+        lat_in(c, c->L, b, g.b64, s);
+        xs = g.x64;
+        bs = g.b64;
+        r = fp64 ? nullptr : g.r64;
+        lat_residual<double>(c, c->L, xs, bs, r, c->scal, s);
+    } else if (tfuse) {
         mirror_refresh<double>(c, c->L, x, s);
         residual_norm_t<double>(c, c->L, x, b, tL, c->scal, s);
     } else {
@@ -1999,17 +2520,19 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
     int stagn = 0;
     hhg_status st = HHG_ENOCONV;
     if (e0) (void)hipEventRecord(e0, s);
-    if (fp64 && !tfuse) mirror_refresh<double>(c, c->L, x, s);
+    if (fp64 && !tfuse && !c->lat) mirror_refresh<double>(c, c->L, x, s);
     int k = 0;
     // one cycle and its stopping-test residual: the same launches every cycle,
     // replayed from a captured graph unless graphs are off or timing is on
     auto body = [&](hipStream_t st) {
         if (!fp64)
-            cycle_mixed(c, x, st);
+            cycle_mixed(c, xs, st);
         else
-            cycle_fp64(c, x, b, st, tfuse);
+            cycle_fp64(c, xs, bs, st, tfuse || c->lat);
         PhaseTimed pt(c, PH_RESIDUAL, c->L, st);
-        if (tfuse)
+        if (c->lat)
+            lat_residual<double>(c, c->L, xs, bs, r, c->scal, st);
+        else if (tfuse)
             residual_norm_t<double>(c, c->L, x, b, tL, c->scal, st);
         else
             residual_norm<double>(c, c->L, x, b, r, c->scal, st, fp64);
@@ -2017,7 +2540,7 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
     for (auto& v : c->ppairs) v.clear();
     c->phase_active = c->phase_timing;
     hhg_ctx::CycleGraph* graph = (c->opts.graphs && !c->timing && !c->phase_timing)
-                                     ? cycle_graph(c, x, b, body)
+                                     ? cycle_graph(c, xs, bs, body)
                                      : nullptr;
     for (k = 1; k <= max_cycles; ++k) {
         if (graph)
@@ -2046,6 +2569,7 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
         if (stagn >= 5) break;
     }
     c->phase_active = false;
+    if (c->lat) lat_out(c, c->L, xs, x, s);
     if (e1) (void)hipEventRecord(e1, s);
     if (e0 && e1) {
         (void)hipEventSynchronize(e1);
@@ -2173,6 +2697,199 @@ const int CK_GDIR[15][3] = {{0, 0, 0},  {1, 0, 0},   {-1, 0, 0}, {0, 1, 0},  {0,
             return false;                                                              \
         }                                                                              \
     } while (0)
+
+// The lattice path's index arithmetic on one level: every interior vertex in
+// one row lane and every surface vertex in one surface lane of each launch,
+// taps, windows and transfers at the intended vertices, every address (those
+// of masked entries too) inside the field, records of the right vertex.
+bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
+    const HostLevel& h = c->H[l];
+    const Lat<double> G = lat_geometry<double>(c, l);
+    const LatLevel& g = c->G[l];
+    const int64_t N = h.N;
+    auto node = [&](int x, int y, int z) { return x + (int64_t)G.nx * (y + (int64_t)G.ny * z); };
+    std::vector<int64_t> at_node(G.len, -1);
+    for (int z = 0; z < G.nz; ++z)
+        for (int y = 0; y < G.ny; ++y)
+            for (int x = 0; x < G.nx; ++x) {
+                const int a = lat_at(G, x, y, z);
+                CK(a >= 0 && (size_t)a < G.len && at_node[a] < 0, "lattice address");
+                at_node[a] = node(x, y, z);
+            }
+    auto holds = [&](int64_t a, int x, int y, int z) {
+        return a >= 0 && (size_t)a < G.len && at_node[a] == node(x, y, z);
+    };
+    auto inside = [&](int64_t a, int w) { return a >= 0 && (size_t)(a + w) <= G.len; };
+    auto surface = [&](int x, int y, int z) {
+        return x == 0 || y == 0 || z == 0 || x == G.nx - 1 || y == G.ny - 1 || z == G.nz - 1;
+    };
+    const int planes = G.nz - 2;
+    const int bs = lat_bs(G);
+    for (int per : {lat_pair_lanes(G, 1), lat_pair_lanes(G, 2), lat_quad_lanes(G)})
+        for (int order = 0; order < 3 && per > 0; ++order) {
+            const LatGrid tg = lat_grid(per, planes, bs);
+            std::vector<int> hit((size_t)tg.per * planes, 0), slot(tg.total, 0);
+            for (int v = 0; v < tg.total; ++v) {
+                const LatTile T = lat_tile(tg, planes, v, order);
+                CK(T.t >= 0 && T.t < tg.total && !slot[T.t]++, "tile index");
+                if (!T.ok) continue;
+                CK(T.z >= 0 && T.part >= 0, "tile out of range");
+                hit[(size_t)T.z * tg.per + T.part]++;
+            }
+            for (int h1 : hit) CK(h1 == 1, "tile not visited once");
+        }
+    const int roff[7] = {0, G.RS, -G.RS, G.ZS, -G.ZS, G.RS + G.ZS, -G.RS - G.ZS};
+    // row lanes of the colour launches
+    for (int NC = 1; NC <= 2; ++NC)
+        for (int col = 0; col < (NC == 2 ? 2 : 4) && l > 0; ++col) {
+            std::vector<uint8_t> seen(N, 0);
+            const LatGrid tg = lat_grid(lat_pair_lanes(G, NC), planes, bs);
+            for (int v = 0; v < tg.total; ++v)
+                for (int lane = 0; lane < bs; ++lane) {
+                    const LatTile t = lat_tile(tg, planes, v, c->opts.block_order);
+                    if (!t.ok) continue;
+                    const LatPair P = NC == 2 ? lat_pair_lane<2>(G, col, tg, t, lane) : lat_pair_lane<1>(G, col, tg, t, lane);
+                    if (!P.ok) continue;
+                    CK(P.z >= 1 && P.z <= G.nz - 2 && P.y >= 1 && P.y <= G.ny - 2, "row lane outside the box");
+                    int xp, xm;
+                    lat_x_offsets(P.s, G.Qp, &xp, &xm);
+                    const int64_t a = (int64_t)(P.z * G.ny + P.y) * G.RS + lat_slot(P.s) * G.Qp + P.q;
+                    for (int o : roff)
+                        CK(inside(a + o, 2) && inside(a + xp + o, 2) && inside(a + xm + o, 2), "row tap out of range");
+                    for (int e = 0; e < 2; ++e) {
+                        const int x = 4 * (P.q + e) + P.s;
+                        if (x == 0) continue;
+                        CK(x <= G.nx - 2 && ((x + P.y + P.z) & (NC == 2 ? 1 : 3)) == col, "row lane's vertex");
+                        CK(!seen[node(x, P.y, P.z)]++, "row vertex visited twice");
+                        CK(holds(a + e, x, P.y, P.z) && holds(a + e + xp, x + 1, P.y, P.z) &&
+                               holds(a + e + xm, x - 1, P.y, P.z) && holds(a + e + G.RS, x, P.y + 1, P.z) &&
+                               holds(a + e - G.ZS, x, P.y, P.z - 1) &&
+                               holds(a + e + xp + G.RS + G.ZS, x + 1, P.y + 1, P.z + 1) &&
+                               holds(a + e + xm - G.RS - G.ZS, x - 1, P.y - 1, P.z - 1),
+                           "row tap holds the wrong vertex");
+                    }
+                }
+            for (int S : {4 / NC}) {
+                const LatSurf B = lat_surface(G, S, 63);
+                for (int i = 0; i < B.beg[6] + 300; ++i) {
+                    int x, y, z;
+                    if (!lat_surf_lane(G, B, S, col, i, &x, &y, &z)) continue;
+                    CK(x >= 0 && y >= 0 && z >= 0 && x < G.nx && y < G.ny && z < G.nz && surface(x, y, z) &&
+                           ((x + y + z) & (S - 1)) == col,
+                       "surface lane's vertex");
+                    CK(!seen[node(x, y, z)]++, "surface vertex visited twice");
+                }
+            }
+            for (int z = 0; z < G.nz; ++z)
+                for (int y = 0; y < G.ny; ++y)
+                    for (int x = 0; x < G.nx; ++x)
+                        CK(seen[node(x, y, z)] == (((x + y + z) & (NC == 2 ? 1 : 3)) == col ? 1 : 0),
+                           "colour launch does not cover its colour");
+        }
+    // quads: windows and the restriction into this level
+    std::vector<uint8_t> seen(N, 0);
+    const LatGrid qg = lat_grid(lat_quad_lanes(G), planes, bs);
+    for (int v = 0; v < qg.total; ++v)
+        for (int lane = 0; lane < bs; ++lane) {
+            const LatTile t = lat_tile(qg, planes, v, c->opts.block_order);
+            if (!t.ok) continue;
+            const LatPair P = lat_quad_lane(G, qg, t, lane);
+            if (!P.ok) continue;
+            CK(P.z >= 1 && P.z <= G.nz - 2 && P.y >= 1 && P.y <= G.ny - 2 && P.q >= 0 && P.q < G.Qi, "quad lane");
+            const int64_t a = (int64_t)(P.z * G.ny + P.y) * G.RS + P.q;
+            for (int r = 0; r < 7; ++r) {
+                const int64_t w = a + roff[r];
+                CK(inside(w, 2) && inside(w + G.Qp, 1) && inside(w + 2 * G.Qp, 1) && inside(w + 3 * G.Qp - 1, 2),
+                   "window out of range");
+                const int dy = r == 1 || r == 5 ? 1 : r == 2 || r == 6 ? -1 : 0, dz = r == 3 || r == 5 ? 1 : r == 4 || r == 6 ? -1 : 0;
+                for (int j = 0; j < 4; ++j)
+                    CK(holds(w + lat_sub(j, G.Qp), 4 * P.q + j, P.y + dy, P.z + dz), "window entry");
+                CK(holds(w + 1, 4 * P.q + 4, P.y + dy, P.z + dz), "window entry ahead");
+                if (P.q > 0) CK(holds(w + 3 * G.Qp - 1, 4 * P.q - 1, P.y + dy, P.z + dz), "window entry behind");
+            }
+            for (int j = 0; j < 4; ++j) {
+                const int x = 4 * P.q + j;
+                if (x > 0) CK(x <= G.nx - 2 && !seen[node(x, P.y, P.z)]++, "quad vertex");
+            }
+            if (l < c->L) {
+                const Lat<double> F = lat_geometry<double>(c, l + 1);
+                const int foff[7] = {0, F.RS, -F.RS, F.ZS, -F.ZS, F.RS + F.ZS, -F.RS - F.ZS};
+                const int64_t fa = (int64_t)(2 * P.z * F.ny + 2 * P.y) * F.RS + 2 * P.q;
+                for (int o : foff)
+                    CK(fa + o >= 0 && (size_t)(fa + o + 3 * F.Qp + 2) <= F.len, "restriction out of range");
+                for (int e = 0; e < 2; ++e)
+                    for (int j = 0; j < 4; ++j)
+                        CK(fa + e + lat_sub(j, F.Qp) == lat_at(F, 8 * P.q + 4 * e + j, 2 * P.y, 2 * P.z),
+                           "restriction tap");
+            }
+        }
+    const LatSurf B = lat_surface(G, 1, 63);
+    for (int i = 0; i < B.beg[6] + 300; ++i) {
+        int x, y, z;
+        if (!lat_surf_lane(G, B, 1, 0, i, &x, &y, &z)) continue;
+        CK(surface(x, y, z) && !seen[node(x, y, z)]++, "surface vertex of a full launch");
+        int nb[15];
+        lat_taps(G, x, y, z, nb);
+        for (int q = 1; q < 15; ++q) {
+            const int X = x + CK_GDIR[q][0], Y = y + CK_GDIR[q][1], Z = z + CK_GDIR[q][2];
+            const bool in = X >= 0 && Y >= 0 && Z >= 0 && X < G.nx && Y < G.ny && Z < G.nz;
+            CK(in ? holds(nb[q], X, Y, Z) : nb[q] == nb[0], "surface tap");
+            const int sid = h.node_sid[node(x, y, z)];
+            if (!in)
+                for (int blk : {ST_A, ST_C, ST_B, ST_B + 15, ST_B + 30, ST_BT, ST_BT + 15, ST_BT + 30})
+                    CK(sid >= 0 && h.st[(size_t)sid * ST_SIZE + blk + q] == 0.0, "tap outside the box has a coefficient");
+        }
+        // a free velocity vertex has its lane in the velocity launches
+        if (!h.node_dir[node(x, y, z)]) {
+            const int f = z == 0 ? 0 : z == G.nz - 1 ? 1 : y == 0 ? 2 : y == G.ny - 1 ? 3 : x == 0 ? 4 : 5;
+            CK(g.svel.beg[f + 1] > g.svel.beg[f], "face without velocity lanes has a free vertex");
+        }
+    }
+    for (int64_t v = 0; v < N; ++v) CK(seen[v] == 1, "full launch does not cover the level");
+    // records: vertices with one index share their stencil record
+    std::vector<int> sid_of((size_t)g.nrid, INT32_MIN);
+    for (int z = 0; z < G.nz; ++z)
+        for (int y = 0; y < G.ny; ++y)
+            for (int x = 0; x < G.nx; ++x) {
+                const int i = lat_rid_index(G, x, y, z);
+                CK(i >= 0 && i < g.nrid, "record index out of range");
+                const int sid = h.node_sid[node(x, y, z)];
+                const bool small = (x & (G.n - 1)) <= 3 && (y & (G.n - 1)) <= 3 && (z & (G.n - 1)) <= 3;
+                if (small) sid_of[i] = sid;
+            }
+    for (int z = 0; z < G.nz; ++z)
+        for (int y = 0; y < G.ny; ++y)
+            for (int x = 0; x < G.nx; ++x)
+                CK(sid_of[lat_rid_index(G, x, y, z)] == h.node_sid[node(x, y, z)], "record of another vertex");
+    // prolongation into this level
+    if (l > 0) {
+        const Lat<double> C = lat_geometry<double>(c, l - 1);
+        for (int z = 0; z < G.nz; ++z)
+            for (int y = 0; y < G.ny; ++y)
+                for (int q = 0; q <= G.Qi; ++q) {
+                    const int by = y & 1, bz = z & 1;
+                    const int64_t lo = (int64_t)(((z - bz) >> 1) * C.ny + ((y - by) >> 1)) * C.RS,
+                                  hi = (int64_t)(((z + bz) >> 1) * C.ny + ((y + by) >> 1)) * C.RS;
+                    for (int e = 0; e < 3; ++e) {
+                        const int X = 2 * q + e;
+                        const int64_t o = lat_slot(X & 3) * C.Qp + (X >> 2);
+                        CK(lo + o >= 0 && (size_t)(lo + o) < C.len && (size_t)(hi + o) < C.len, "prolongation out of range");
+                        if (X < C.nx)
+                            CK(lo + o == lat_at(C, X, (y - by) >> 1, (z - bz) >> 1) &&
+                                   hi + o == lat_at(C, X, (y + by) >> 1, (z + bz) >> 1),
+                               "prolongation source");
+                    }
+                    const int64_t a = (int64_t)(z * G.ny + y) * G.RS + q;
+                    for (int j = 0; j < 4; ++j) CK(inside(a + lat_sub(j, G.Qp), 1), "prolongation target");
+                    CK(lat_div(y * (G.Qi + 1) + q, 1.0f / (float)(G.Qi + 1)) == y, "row division");
+                }
+    }
+    for (int i = 0; i < G.nx * G.ny; ++i)
+        CK(lat_div(i, 1.0f / (float)G.nx) == i / G.nx, "row division of the conversion");
+    CK(qg.total + lat_sblocks(B, bs) <= c->npartials && ((G.Qi + 1) * G.ny + 255) / 256 * G.nz <= c->npartials,
+       "partials too small for the lattice path");
+    return true;
+}
 
 bool check_level(const hhg_ctx* c, int l, std::string* err) {
     const HostLevel& h = c->H[l];
@@ -2456,6 +3173,7 @@ bool check_level(const hhg_ctx* c, int l, std::string* err) {
             }
         }
     }
+    if (c->lat && !check_lattice(c, l, err)) return false;
     // grids fit the reduction buffers
     CK(full_blocks((int)h.vtiles.size()) + (h.nif + TPB - 1) / TPB <= c->npartials, "partials too small");
     CK((int)h.ctiles.size() <= c->npartials, "gradient partials too small");
