@@ -100,10 +100,14 @@ struct DevLevelArrays {
 struct LatLevel {
     int* rid = nullptr;
     unsigned char* rdir = nullptr;
+    double* cls64 = nullptr;
+    float* cls32 = nullptr;
     double *rec64 = nullptr, *axr64 = nullptr, *x64 = nullptr, *b64 = nullptr, *r64 = nullptr;
     float *rec32 = nullptr, *axr32 = nullptr, *x32 = nullptr, *b32 = nullptr, *r32 = nullptr;
     int nrec = 0, nrid = 0;
     LatSurf svel, spres, sfull;   // surface lanes of velocity, pressure and full launches
+    // one-workgroup visits (k_lat_visit): 0 no, otherwise the variant
+    int visit64 = 0, visit32 = 0;
 };
 
 constexpr int KV_N = 10;   // finest-level vectors of the Krylov solvers
@@ -131,6 +135,7 @@ struct hhg_ctx {
     CoarseDev cd{};
     // lattice path: the cycles run on the structured lattice (lattice.hpp)
     bool lat = false;
+    size_t lat_lds = 65536;        // LDS of a workgroup
     int lat_kind = 0;              // 0: one viscosity, 1: per-macro viscosities
     std::vector<LatLevel> G;
     std::vector<Lat<double>> G64;
@@ -450,6 +455,8 @@ size_t layout(hhg_ctx* c, char* ws) {
             g.rdir = cv.take<unsigned char>(g.nrec);
             g.rec64 = cv.take<double>((size_t)g.nrec * LR_SIZE);
             g.axr64 = cv.take<double>((size_t)g.nrec * LX_SIZE);
+            g.cls64 = cv.take<double>(27 * LC_SIZE);
+            if (mixed) g.cls32 = cv.take<float>(27 * LC_SIZE);
             const size_t v4 = 4 * G.len;
             if (!mixed || l == c->L) {
                 g.x64 = cv.take<double>(v4);
@@ -585,6 +592,7 @@ hhg_status coarse_direct_setup(hhg_ctx* c) {
 }
 
 // Records and constants of the lattice path (with every change of viscosity).
+hhg_status lat_visit_setup(hhg_ctx* c);
 hhg_status upload_lattice(hhg_ctx* c) {
     if (!c->lat) return HHG_OK;
     c->lat_kind = 0;
@@ -599,6 +607,7 @@ hhg_status upload_lattice(hhg_ctx* c) {
         std::vector<double> rec((size_t)g.nrec * LR_SIZE, 0.0), axr((size_t)g.nrec * LX_SIZE, 0.0);
         std::vector<unsigned char> dir(g.nrec, 0);
         std::vector<int> rid(g.nrid, 0);
+        std::vector<double> cls(27 * LC_SIZE, 0.0);
         for (int r = 0; r < g.nrec; ++r) {
             const double* st = r < h.nm ? &h.st_vol_global[(size_t)r * ST_SIZE] : &h.st[(size_t)r * ST_SIZE];
             double* o = &rec[(size_t)r * LR_SIZE];
@@ -633,6 +642,11 @@ hhg_status upload_lattice(hhg_ctx* c) {
                     const int sid = h.node_sid[v] < 0 ? -h.node_sid[v] - 1 : h.node_sid[v];
                     rid[lat_rid_index(G, X, Y, Z)] = sid;
                     if (h.node_dir[v]) dir[sid] = 1;
+                    double* cr = &cls[(size_t)lat_class(G, X, Y, Z) * LC_SIZE];
+                    for (int q = 0; q < 45; ++q) {
+                        cr[LC_B + q] = rec[(size_t)sid * LR_SIZE + LR_B + q];
+                        cr[LC_BT + q] = rec[(size_t)sid * LR_SIZE + LR_BT + q];
+                    }
                 }
         // constants of the interior vertices (pair symmetries as in the
         // volume records)
@@ -655,6 +669,7 @@ hhg_status upload_lattice(hhg_ctx* c) {
         if ((s = upload<unsigned char>(c, g.rdir, dir.data(), dir.size())) != HHG_OK) return s;
         if ((s = upload<double>(c, g.rec64, rec.data(), rec.size())) != HHG_OK) return s;
         if ((s = upload<double>(c, g.axr64, axr.data(), axr.size())) != HHG_OK) return s;
+        if ((s = upload<double>(c, g.cls64, cls.data(), cls.size())) != HHG_OK) return s;
         Lat<float> F = lat_geometry<float>(c, l);
         for (int q = 0; q < 3; ++q) {
             F.a[q] = (float)G.a[q];
@@ -672,7 +687,11 @@ hhg_status upload_lattice(hhg_ctx* c) {
         G.axr = g.axr64;
         F.rec = g.rec32;
         F.axr = g.axr32;
+        G.cls = g.cls64;
+        F.cls = g.cls32;
         if (g.rec32) {
+            std::vector<float> c32(cls.begin(), cls.end());
+            if ((s = upload<float>(c, g.cls32, c32.data(), c32.size())) != HHG_OK) return s;
             std::vector<float> r32(rec.begin(), rec.end()), a32(axr.begin(), axr.end());
             if ((s = upload<float>(c, g.rec32, r32.data(), r32.size())) != HHG_OK) return s;
             if ((s = upload<float>(c, g.axr32, a32.data(), a32.size())) != HHG_OK) return s;
@@ -680,7 +699,7 @@ hhg_status upload_lattice(hhg_ctx* c) {
         c->G64[l] = G;
         c->G32[l] = F;
     }
-    return HHG_OK;
+    return lat_visit_setup(c);
 }
 
 hhg_status upload_stencils(hhg_ctx* c) {
@@ -1783,6 +1802,150 @@ void lat_uzawa(hhg_ctx* c, int l, T* x, const T* b, T* r, hipStream_t s, bool pz
         for (int col = nc - 1; col >= 0; --col) lat_pres<T>(c, l, col, x, sx, s);
 }
 
+typedef LdsGeom<17, 17> Lds17;
+typedef LdsGeom<33, 9> Lds33;
+typedef LdsGeom<33, 17> Lds33w;
+
+// How one workgroup visits the level in values of `size` bytes (LatLevel),
+// 0 if its iterate does not fit the LDS or its lanes do not reach
+template <typename GEO>
+int lat_visit_geo(const Lat<double>& G, size_t size, size_t lds, int quads, int rim) {
+    const GEO g{G.nx, G.ny, G.nz};
+    if (!g.holds() || (size_t)g.values() * size > lds) return 0;
+    int w = 0;
+    for (int f = 0; f < 7; ++f) w += lat_rim_waves(g, f);
+    return G.Qi * (G.ny - 2) * (G.nz - 2) <= quads * LDS_TPB && w <= rim * LDS_WAVES;
+}
+int lat_visit_lanes(const Lat<double>& G, size_t size, size_t lds) {
+    if (lat_visit_geo<Lds17>(G, size, lds, 1, 2))
+        return (G.nx - 2) * (G.ny - 2) * (G.nz - 2) <= LDS_TPB ? 1 : 2;
+    if (lat_visit_geo<Lds33>(G, size, lds, 1, 2)) return 3;
+    return size == 4 && lat_visit_geo<Lds33w>(G, size, lds, 2, 3) ? 4 : 0;
+}
+
+template <typename T>
+inline int lat_visit_of(const LatLevel& g) { return sizeof(T) == 8 ? g.visit64 : g.visit32; }
+
+template <typename T, int KIND, int S, typename GEO, int V, int QR, int SR>
+hipError_t lat_visit_launch(hhg_ctx* c, int l, const T* b, T* x, T* r, int steps, bool zero, bool res, const LatProg& prog,
+                            hipStream_t s, bool setup) {
+    if (setup)
+        return hipFuncSetAttribute((const void*)k_lat_visit<T, KIND, S, GEO, V, QR, SR>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lat_lds);
+    const LatVecs<T> v = lat_vecs<T>(c, l);
+    const size_t lds = sizeof(T) * GEO{v.G.nx, v.G.ny, v.G.nz}.values();
+    hipLaunchKernelGGL((k_lat_visit<T, KIND, S, GEO, V, QR, SR>), dim3(1), dim3(LDS_TPB), lds, s, v.G, b, x, r, steps,
+                       zero ? 1 : 0, v.g.svel.beg[6] > 0 ? 1 : 0, res ? 1 : 0, prog,
+                       (T)c->opts.omega);
+    return hipSuccess;
+}
+template <typename T>
+hipError_t lat_visit_any(hhg_ctx* c, int l, int lanes, const T* b, T* x, T* r, int steps, bool zero, bool res,
+                         const LatProg& prog, hipStream_t s, bool setup) {
+    const bool rb = c->opts.ordering == 2;
+#define LAT_VISIT(K, S, ...) \
+    lat_visit_launch<T, K, S, __VA_ARGS__>(c, l, b, x, r, steps, zero, res, prog, s, setup)
+#define LAT_VISITS(...)                                                                            \
+    do {                                                                                           \
+        if (c->lat_kind == 0) return rb ? LAT_VISIT(0, 2, __VA_ARGS__) : LAT_VISIT(0, 4, __VA_ARGS__); \
+        return rb ? LAT_VISIT(1, 2, __VA_ARGS__) : LAT_VISIT(1, 4, __VA_ARGS__);                   \
+    } while (0)
+    if (lanes == 1) LAT_VISITS(Lds17, 1, 1, 2);
+    if (lanes == 2) LAT_VISITS(Lds17, 4, 1, 2);
+    if constexpr (sizeof(T) == 4)
+        if (lanes == 4) LAT_VISITS(Lds33w, 4, 2, 3);
+    LAT_VISITS(Lds33, 4, 1, 2);
+#undef LAT_VISITS
+#undef LAT_VISIT
+}
+
+// which levels are visited by one workgroup (with every change of viscosity:
+// the kind of the kernels may change)
+hhg_status lat_visit_setup(hhg_ctx* c) {
+    int dev = 0, lds = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        lds = 65536;
+    c->lat_lds = lds;
+    for (int l = 1; l <= c->L; ++l) {
+        LatLevel& g = c->G[l];
+        const Lat<double> G = lat_geometry<double>(c, l);
+        g.visit64 = lat_visit_lanes(G, 8, c->lat_lds);
+        // FP64 levels of more than 1024 interior vertices in the red-black
+        // order: five launches take 19.5 us for 17^3 vertices, a visit's step 21
+        // (one CU's LDS and FP64 rate); eleven launches of the colour order
+        // take 42 us, its step 30
+        if (g.visit64 > 1 && c->opts.ordering == 2) g.visit64 = 0;
+        g.visit32 = c->opts.precision == 1 ? lat_visit_lanes(G, 4, c->lat_lds) : 0;
+        if (g.visit64)
+            HIPCHECK(c, lat_visit_any<double>(c, l, g.visit64, nullptr, nullptr, nullptr, 0, false, false, LatProg{},
+                                              nullptr, true));
+        if (g.visit32)
+            HIPCHECK(c, lat_visit_any<float>(c, l, g.visit32, nullptr, nullptr, nullptr, 0, false, false, LatProg{},
+                                             nullptr, true));
+    }
+    return HHG_OK;
+}
+
+// `steps` Uzawa steps on a level that one workgroup visits, and with res the
+// residual into r.  With the kernel-class timers on, the finest level's sweeps
+// run one to a launch.
+template <typename T>
+void lat_visit(hhg_ctx* c, int l, T* x, const T* b, T* r, int steps, bool zero, bool given, bool res,
+               hipStream_t s) {
+    const int lanes = lat_visit_of<T>(c->G[l]), ps = c->opts.p_sweep;
+    const bool rb = c->opts.ordering == 2;
+    const bool timed = c->timing && l == c->L;
+    ops(c, l, steps * (rb ? 1.5 : 1.75), 2.0 * steps - (given && steps > 0 ? 1 : 0), steps * (1.0 + ps), 0);
+    static const unsigned char rorder[3] = {0, 1, 0}, corder[7] = {0, 1, 2, 3, 2, 1, 0};
+    const unsigned char* order = rb ? rorder : corder;
+    const int nv = rb ? 3 : 7, nc = rb ? 2 : 4;
+    LatProg prog{};
+    auto put = [](LatProg& p, int op) { p.op[p.n++] = (unsigned char)op; };
+    put(prog, LOP_T);
+    for (int i = 0; i < nv; ++i) put(prog, LOP_V + order[i]);
+    put(prog, LOP_S);
+    for (int col = 0; col < nc; ++col) put(prog, LOP_P + col);
+    if (ps)
+        for (int col = nc - 1; col >= 0; --col) put(prog, LOP_P + col);
+    if (!timed) {
+        (void)lat_visit_any<T>(c, l, lanes, b, x, r, steps, zero, res, prog, s, false);
+    } else {
+        auto one = [&](int cls, int rows, int op, double bytes, bool z) {
+            LatProg p{};
+            put(p, rows);
+            put(p, op);
+            Timed tm(c, cls, s, true, bytes);
+            (void)lat_visit_any<T>(c, l, lanes, b, x, r, 1, z, false, p, s, false);
+        };
+        for (int q = 0; q < steps; ++q) {
+            auto vel = [&](int i, int cls) {
+                const int col = order[i];
+                one(cls, LOP_T, LOP_V + col, rb ? c->lbytes_vel[col] + c->lbytes_vel[col + 2] : c->lbytes_vel[col],
+                    zero && q == 0 && i == 0);
+            };
+            auto pres = [&](int col, int cls) {
+                one(cls, LOP_S, LOP_P + col,
+                    cls == HHG_K_APPLY ? c->bytes_bp_fused[rb ? 4 : 0]
+                    : rb               ? c->bytes_pres[col] + c->bytes_pres[col + 2]
+                                       : c->bytes_pres[col],
+                    false);
+            };
+            const bool g0 = given && q == 0;
+            if (!g0) vel(0, HHG_K_RU);
+            {
+                TimedGroup tg(c, HHG_K_VEL, s, true);
+                for (int i = g0 ? 0 : 1; i < nv; ++i) vel(i, HHG_K_VEL);
+            }
+            for (int col = 0; col < nc; ++col) pres(col, col == 0 ? HHG_K_APPLY : HHG_K_PRES);
+            if (ps)
+                for (int col = nc - 1; col >= 0; --col) pres(col, HHG_K_PRES);
+        }
+        if (res) (void)lat_visit_any<T>(c, l, lanes, b, x, r, 0, false, true, prog, s, false);
+    }
+    if (res) ops(c, l, 1, 2, 1, 0);
+}
+
 // r = b - K x on level l; out: its norm; r NULL: the norm alone
 template <typename T>
 void lat_residual(hhg_ctx* c, int l, const T* x, const T* b, T* r, double* out, hipStream_t s) {
@@ -1838,12 +2001,16 @@ template <typename T>
 void lat_vcycle(hhg_ctx* c, int l, int top, T* x, const T* b, hipStream_t s, bool zero, bool given) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const int extra = c->opts.cycle == 1 ? 2 * (top - l) : 0;
+    const bool visit = lat_visit_of<T>(v.g) != 0;
     {
         PhaseTimed pt(c, PH_SMOOTH, l, s);
-        for (int q = 0; q < c->opts.nu1 + extra; ++q)
-            lat_uzawa<T>(c, l, x, b, v.r, s, zero && q == 0, given && q == 0);
+        if (visit)
+            lat_visit<T>(c, l, x, b, v.r, c->opts.nu1 + extra, zero, given, true, s);
+        else
+            for (int q = 0; q < c->opts.nu1 + extra; ++q)
+                lat_uzawa<T>(c, l, x, b, v.r, s, zero && q == 0, given && q == 0);
     }
-    {
+    if (!visit) {
         PhaseTimed pt(c, PH_RESIDUAL, l, s);
         lat_residual<T>(c, l, x, b, v.r, nullptr, s);
     }
@@ -1866,6 +2033,10 @@ void lat_vcycle(hhg_ctx* c, int l, int top, T* x, const T* b, hipStream_t s, boo
         lat_prolong<T, false>(c, l, w.x, x, s);
     }
     PhaseTimed pt(c, PH_SMOOTH, l, s);
+    if (visit) {
+        if (c->opts.nu2 + extra > 0) lat_visit<T>(c, l, x, b, v.r, c->opts.nu2 + extra, false, false, false, s);
+        return;
+    }
     for (int q = 0; q < c->opts.nu2 + extra; ++q) lat_uzawa<T>(c, l, x, b, v.r, s, false, false);
 }
 
@@ -2702,6 +2873,79 @@ const int CK_GDIR[15][3] = {{0, 0, 0},  {1, 0, 0},   {-1, 0, 0}, {0, 1, 0},  {0,
 // one row lane and every surface vertex in one surface lane of each launch,
 // taps, windows and transfers at the intended vertices, every address (those
 // of masked entries too) inside the field, records of the right vertex.
+template <typename GEO>
+bool check_visit(const hhg_ctx* c, int l, const GEO& D, std::string* err) {
+    if (!D.holds()) return true;
+    const Lat<double> G = lat_geometry<double>(c, l);
+    const int N = D.field();
+    auto surface = [&](int x, int y, int z) {
+        return x == 0 || y == 0 || z == 0 || x == G.nx - 1 || y == G.ny - 1 || z == G.nz - 1;
+    };
+    auto node = [&](int x, int y, int z) { return x + G.nx * (y + G.ny * z); };
+    std::vector<int> in_lds(N, -1), seen(c->H[l].N, 0);
+    for (int z = 0; z < G.nz; ++z)
+        for (int y = 0; y < G.ny; ++y)
+            for (int x = 0; x < G.nx; ++x) {
+                const int a = D.at(x, y, z);
+                CK(a >= 0 && a < N && in_lds[a] < 0, "LDS address");
+                in_lds[a] = node(x, y, z);
+                // taps in any direction stay between the pads
+                int P, M;
+                lds_x_offsets<GEO>(x & 3, &P, &M);
+                for (int o : {0, D.SX, -D.SX, D.PS, -D.PS, D.SX + D.PS, -D.SX - D.PS})
+                    for (int q : {0, P, M})
+                        CK(a + o + q >= -D.PAD && a + o + q < N + D.PAD, "visit's tap out of range");
+            }
+    for (int i = 0; i < (G.nx - 2) * (G.ny - 2) * (G.nz - 2) + 100; ++i) {
+        int x, y, z;
+        if (!lat_visit_item<1>(D, i, &x, &y, &z)) {
+            CK(x >= 0 && y >= 0 && z >= 0 && x < G.nx && y < G.ny && z < G.nz, "visit's idle lane");
+            continue;
+        }
+        CK(!surface(x, y, z) && !seen[node(x, y, z)]++, "visit's interior vertex");
+        int P, M;
+        lds_x_offsets<GEO>(x & 3, &P, &M);
+        CK(in_lds[D.at(x, y, z) + P] == node(x + 1, y, z) && in_lds[D.at(x, y, z) + M] == node(x - 1, y, z),
+           "visit's tap");
+    }
+    for (int z = 1; z < G.nz - 1; ++z)
+        for (int y = 1; y < G.ny - 1; ++y)
+            for (int x = 1; x < G.nx - 1; ++x) CK(seen[node(x, y, z)]-- == 1, "visit's interior vertices");
+    for (int i = 0; i < G.Qi * (G.ny - 2) * (G.nz - 2) + 100; ++i) {
+        int x0, y, z;
+        if (!lat_visit_item<4>(D, i, &x0, &y, &z)) continue;
+        CK(x0 % 4 == 0, "visit's quad");
+        const int a = D.at(x0, y, z);
+        for (int j = 0; j < 4; ++j) {
+            const int x = x0 + j;
+            if (x == 0) continue;
+            CK(!surface(x, y, z) && !seen[node(x, y, z)]++, "visit's quad vertex");
+            CK(in_lds[a + D.off(j)] == node(x, y, z), "visit's quad entry");
+        }
+        CK(in_lds[a + 1] == node(x0 + 4, y, z) && (x0 == 0 || in_lds[a + D.off(3) - 1] == node(x0 - 1, y, z)),
+           "visit's quad neighbours");
+    }
+    int waves = 0;
+    for (int f = 0; f < 7; ++f) waves += lat_rim_waves(D, f);
+    for (int i = 0; i < 64 * waves + 300; ++i) {
+        int x = 0, y = 0, z = 0;
+        if (!lat_rim_lane(D, i, &x, &y, &z)) {
+            CK(!lat_rim_is_face(D, i >> 6) || (i & 63), "face wave without a first vertex");
+            continue;
+        }
+        const bool face = (x == 0 || x == G.nx - 1) + (y == 0 || y == G.ny - 1) + (z == 0 || z == G.nz - 1) == 1;
+        CK(lat_rim_is_face(D, i >> 6) == face, "visit's face waves");
+        if (face) {
+            int x0, y0, z0;
+            CK(lat_rim_lane(D, i & ~63, &x0, &y0, &z0) && lat_class(G, x0, y0, z0) == lat_class(G, x, y, z),
+               "visit's face class");
+        }
+        CK(surface(x, y, z) && !seen[node(x, y, z)]++, "visit's surface vertex");
+    }
+    for (int64_t v = 0; v < c->H[l].N; ++v) CK(seen[v] == 1, "visit does not cover the level");
+    return true;
+}
+
 bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
     const HostLevel& h = c->H[l];
     const Lat<double> G = lat_geometry<double>(c, l);
@@ -2846,6 +3090,9 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
         }
     }
     for (int64_t v = 0; v < N; ++v) CK(seen[v] == 1, "full launch does not cover the level");
+    if (!check_visit(c, l, Lds17{G.nx, G.ny, G.nz}, err) || !check_visit(c, l, Lds33{G.nx, G.ny, G.nz}, err) ||
+        !check_visit(c, l, Lds33w{G.nx, G.ny, G.nz}, err))
+        return false;
     // records: vertices with one index share their stencil record
     std::vector<int> sid_of((size_t)g.nrid, INT32_MIN);
     for (int z = 0; z < G.nz; ++z)

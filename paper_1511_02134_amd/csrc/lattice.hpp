@@ -21,6 +21,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "hhg_internal.hpp"
 
 namespace hhg {
@@ -30,6 +32,9 @@ constexpr int LR_A = 0, LR_C = 15, LR_B = 30, LR_BT = 75, LR_INVA = 120, LR_INVC
               LR_SIZE = 124;
 constexpr int LX_A = 0, LX_INVA = 6, LX_C = 8, LX_C0 = 14, LX_INVC = 15, LX_A0 = 7, LX_SIZE = 16;
 constexpr int LPAT = 216;   // record patterns per cell
+// B and B^T rows by surface class (which faces of the box hold the vertex):
+// they do not depend on the viscosity
+constexpr int LC_B = 0, LC_BT = 45, LC_SIZE = 90;
 
 template <typename T>
 struct Lat {
@@ -43,6 +48,7 @@ struct Lat {
     const T* rec;               // [nrec][LR_SIZE]
     const T* axr;               // [nrec][LX_SIZE]
     const unsigned char* rdir;  // [nrec] 1: velocity Dirichlet
+    const T* cls;               // [27][LC_SIZE]
     // interior constants: axis pairs of A and C (KIND 0), B^T_k over the seven
     // opposite pairs (+d minus -d; B_k is its negative), lumped mass
     T a[3], inva, a0, c[3], invc, c0, bt[3][7], mass;
@@ -80,6 +86,12 @@ __host__ __device__ __forceinline__ int lat_rid_index(const Lat<T>& L, int x, in
     const int a = (fx > fy) - (fx < fy) + 1, b = (fy > fz) - (fy < fz) + 1, c = (fx > fz) - (fx < fz) + 1;
     return cell * LPAT + ((a * 3 + b) * 3 + c) * 8 + (fx == 0 ? 1 : 0) + (fy == 0 ? 2 : 0) +
            (fz == 0 ? 4 : 0);
+}
+
+template <typename T>
+__host__ __device__ __forceinline__ int lat_class(const Lat<T>& L, int x, int y, int z) {
+    return (x == 0 ? 0 : x == L.nx - 1 ? 2 : 1) + 3 * (y == 0 ? 0 : y == L.ny - 1 ? 2 : 1) +
+           9 * (z == 0 ? 0 : z == L.nz - 1 ? 2 : 1);
 }
 
 // item / d for items below 2^21 (host-checked), inv = 1 / d
@@ -817,6 +829,628 @@ __global__ void __launch_bounds__(256) k_lat_out(Lat<T> L, const int* __restrict
     const int a = lat_at(L, X, y, z);
 #pragma unroll
     for (int f = 0; f < 4; ++f) v[f * plen + s] = (double)x[f * L.len + a];
+}
+
+// ---------------------------------------------------------------------------
+// Levels whose iterate fits the LDS of one CU: all smoothing steps of a visit
+// in one workgroup of 16 waves, with barriers instead of launches, and the
+// residual after the last step.  On such a level a launch is all latency (3 to
+// 5 us for a few thousand vertices; five launches per Uzawa step in the
+// red-black order, eleven in the colour order).  A lane owns one interior quad
+// (x = 4 q .. 4 q + 3) and keeps its rows f - B^T p and B u - g in registers,
+// ordered by colour; surface vertices are dealt out face by face, so that a
+// wave's records are the same and come from scalar loads.
+// Measured, FP64, an Uzawa step: 9^3 vertices 7 us red-black, 13 us colours
+// (launches: 19 and 42), bound by latency; 17^3 vertices 21 and 30 us (19.5 and
+// 42), bound by one CU's LDS (two thirds of the cycles, half of them bank
+// conflicts) and FP64 rate.
+// ---------------------------------------------------------------------------
+// LDS layout of a visit: rows of SX values (sub-row 0 first with one entry more
+// than the others), planes of SX SY.  The strides are constants, so that a tap is
+// an immediate offset of its vertex; smaller boxes leave entries unused.  A pad
+// in front and behind keeps the taps of surface vertices that leave the box in
+// range: their coefficients are 0 and every value there is finite.
+template <int SX_, int SY_>
+struct LdsGeom {
+    static constexpr int SX = SX_, PS = SX_ * SY_, Q = (SX_ - 1) / 4, PAD = PS + SX_ + 1;
+    int nx, ny, nz;
+    __host__ __device__ static constexpr int off(int s) { return s * Q + (s > 0 ? 1 : 0); }
+    __host__ __device__ int at(int x, int y, int z) const { return z * PS + y * SX + off(x & 3) + (x >> 2); }
+    __host__ __device__ int field() const { return PS * nz; }
+    __host__ __device__ int values() const { return 4 * field() + 2 * PAD; }
+    __host__ __device__ bool holds() const { return nx <= SX_ && ny <= SY_; }
+};
+
+// Surface lane i of a visit: faces z0, z1, y0, y1, x0, x1 without their edges,
+// each padded to whole waves, then edges and corners.
+template <typename G>
+__host__ __device__ __forceinline__ int lat_rim_waves(const G& g, int f) {
+    const int a = f < 4 ? g.nx - 2 : g.ny - 2, b = f < 2 ? g.ny - 2 : g.nz - 2;
+    if (f < 6) return (a * b + 63) / 64;
+    return (4 * (g.nx + g.ny + g.nz - 6) + 8 + 63) / 64;
+}
+template <typename G>
+__host__ __device__ __forceinline__ bool lat_rim_lane(const G& g, int i, int* x, int* y, int* z) {
+    int w = i >> 6, f = 0;
+    for (; f < 7; ++f) {
+        const int c = lat_rim_waves(g, f);
+        if (w < c) break;
+        w -= c;
+    }
+    if (f == 7) return false;
+    int k = (w << 6) + (i & 63);
+    if (f < 6) {
+        const int a = f < 4 ? g.nx - 2 : g.ny - 2, b = f < 2 ? g.ny - 2 : g.nz - 2;
+        if (k >= a * b) return false;
+        const int r = k / a, s = k - r * a;
+        *x = f < 4 ? s + 1 : f == 4 ? 0 : g.nx - 1;
+        *y = f < 2 ? r + 1 : f == 2 ? 0 : f == 3 ? g.ny - 1 : s + 1;
+        *z = f == 0 ? 0 : f == 1 ? g.nz - 1 : r + 1;
+        return true;
+    }
+    if (k < 8) {
+        *x = k & 1 ? g.nx - 1 : 0;
+        *y = k & 2 ? g.ny - 1 : 0;
+        *z = k & 4 ? g.nz - 1 : 0;
+        return true;
+    }
+    k -= 8;
+    const int n0 = 4 * (g.nx - 2), n1 = 4 * (g.ny - 2), n2 = 4 * (g.nz - 2);
+    const int c = k & 3, m = k >> 2;
+    if (k < n0) {
+        *x = m + 1;
+        *y = c & 1 ? g.ny - 1 : 0;
+        *z = c & 2 ? g.nz - 1 : 0;
+        return true;
+    }
+    if (k < n0 + n1) {
+        *y = m - (g.nx - 2) + 1;
+        *x = c & 1 ? g.nx - 1 : 0;
+        *z = c & 2 ? g.nz - 1 : 0;
+        return true;
+    }
+    if (k < n0 + n1 + n2) {
+        *z = m - (g.nx - 2) - (g.ny - 2) + 1;
+        *x = c & 1 ? g.nx - 1 : 0;
+        *y = c & 2 ? g.ny - 1 : 0;
+        return true;
+    }
+    return false;
+}
+
+// surface wave w of a visit lies in a face (its lanes share their class)
+template <typename G>
+__host__ __device__ __forceinline__ bool lat_rim_is_face(const G& g, int w) {
+    int c = 0;
+    for (int f = 0; f < 6; ++f) c += lat_rim_waves(g, f);
+    return w < c;
+}
+// Interior item i: V = 4 the quad that starts at (*x, *y, *z), V = 1 a vertex.
+// Rows four apart come first: with 17 values to an LDS row, eight of them then
+// fall into distinct banks.
+template <int V, typename G>
+__host__ __device__ __forceinline__ bool lat_visit_item(const G& g, int i, int* x, int* y, int* z) {
+    const int w = V == 4 ? (g.nx - 1) / 4 : g.nx - 2, row = i / w, h = g.ny - 2;
+    const int zz = row / h, yy = row - zz * h;
+    const bool ok = zz < g.nz - 2;
+    // yy counts 0, 4, 8, .., 1, 5, 9, ..
+    int r = yy, c = 0;
+    for (; c < 3; ++c) {
+        const int m = (h + 3 - c) >> 2;
+        if (r < m) break;
+        r -= m;
+    }
+    *x = ok ? (V == 4 ? 4 * (i - row * w) : i - row * w + 1) : 0;
+    *y = ok ? 4 * r + c + 1 : 1;
+    *z = ok ? zz + 1 : 1;
+    return ok;
+}
+
+// rows of a group around a quad: a[e + 1] of the row ahead (the quad's own row
+// in group 0), b[e + 1] of the row behind, e = -1 .. 4
+template <typename T>
+struct LdsRows {
+    T a[6], b[6];
+};
+template <typename GEO, int G, typename T>
+__device__ __forceinline__ void lds_rows(const T* f, LdsRows<T>& R) {
+    constexpr int o = G == 0 ? 0 : G == 1 ? GEO::SX : G == 2 ? GEO::PS : GEO::SX + GEO::PS;
+    constexpr int o1 = GEO::off(1), o2 = GEO::off(2), o3 = GEO::off(3);
+    const T* p = f + o;
+    R.a[1] = p[0];
+    R.a[2] = p[o1];
+    R.a[3] = p[o2];
+    R.a[4] = p[o3];
+    R.a[5] = p[1];
+    if (G == 0) {
+        R.a[0] = p[o3 - 1];
+    } else {
+        const T* m = f - o;
+        R.b[0] = m[o3 - 1];
+        R.b[1] = m[0];
+        R.b[2] = m[o1];
+        R.b[3] = m[o2];
+        R.b[4] = m[o3];
+    }
+}
+// acc[j] += w0 (first pair of the group) + w1 (second pair)
+template <int G, typename T>
+__device__ __forceinline__ void lds_diff(const LdsRows<T>& R, T w0, T w1, T acc[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (G == 0)
+            acc[j] += w0 * (R.a[j + 2] - R.a[j]);
+        else
+            acc[j] += w0 * (R.a[j + 1] - R.b[j + 1]) + w1 * (R.a[j + 2] - R.b[j]);
+    }
+}
+// pairs of group G
+__host__ __device__ constexpr int lat_gp0(int G) { return G == 0 ? 0 : G == 1 ? 1 : G == 2 ? 2 : 4; }
+__host__ __device__ constexpr int lat_gp1(int G) { return G == 0 ? 0 : G == 1 ? 3 : G == 2 ? 5 : 6; }
+
+// v[e] <- v[(e + r) & 3]: rows by position in the quad -> rows by colour
+template <typename T>
+__device__ __forceinline__ void lat_rotate(T v[4], int r) {
+    const T a0 = r & 1 ? v[1] : v[0], a1 = r & 1 ? v[2] : v[1], a2 = r & 1 ? v[3] : v[2],
+            a3 = r & 1 ? v[0] : v[3];
+    v[0] = r & 2 ? a2 : a0;
+    v[1] = r & 2 ? a3 : a1;
+    v[2] = r & 2 ? a0 : a2;
+    v[3] = r & 2 ? a1 : a3;
+}
+
+// LDS offsets of x + 1 and x - 1 from a vertex of sub-row s
+template <typename GEO>
+__host__ __device__ __forceinline__ void lds_x_offsets(int s, int* P, int* M) {
+    constexpr int q = GEO::Q;
+    *P = s == 3 ? -3 * q : s == 0 ? q + 1 : q;
+    *M = s == 0 ? 3 * q : s == 1 ? -q - 1 : -q;
+}
+
+template <typename T>
+using LatConst = const __attribute__((address_space(4))) T*;
+
+// passes of a visit: the rows f - B^T p, the rows B u - g, the velocity sweep of
+// colour (parity) op - LOP_V, the pressure sweep of colour op - LOP_P
+enum { LOP_T = 0, LOP_S = 1, LOP_V = 4, LOP_P = 8 };
+struct LatProg {
+    int n;
+    unsigned char op[24];
+};
+
+constexpr int LDS_WAVES = 16, LDS_TPB = 64 * LDS_WAVES;
+
+// V: vertices of an interior item, 4 (quads) or 1 (levels with at most 1024
+// interior vertices: more waves share the latency); QR, SR: interior items and
+// surface vertices per lane (at most).  S = 2: red-black, 4: colours.  zero: x =
+// 0 on entry; rim: some surface vertex has a free velocity; res: r = b - K x
+// after the last step.  prog: the passes of a step.
+template <typename T, int KIND, int S, typename GEO, int V, int QR, int SR>
+__global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __restrict__ b,
+                                                       T* __restrict__ x, T* __restrict__ r, int steps,
+                                                       int zero, int rim, int res, LatProg prog, T omega) {
+    extern __shared__ char lds_raw[];
+    const size_t len = L.len;
+    const GEO g{L.nx, L.ny, L.nz};
+    constexpr int SX = GEO::SX, PS = GEO::PS;
+    const int N = g.field(), tid = (int)threadIdx.x;
+    T* f0 = reinterpret_cast<T*>(lds_raw) + GEO::PAD;
+    T* pr = f0 + 3 * N;
+    for (int i = tid; i < g.values(); i += LDS_TPB) f0[i - GEO::PAD] = T(0);
+    __syncthreads();
+    // whole rows in and out
+    auto copy = [&](auto body) __attribute__((always_inline)) {
+        for (int i = tid; i < g.nx * g.ny * g.nz; i += LDS_TPB) {
+            const int row = i / g.nx, e = i - row * g.nx, z = row / g.ny, y = row - z * g.ny;
+            const int s = e <= L.Qi ? 0 : (e - 1) / L.Qi, q = e - s * L.Qi - (s > 0 ? 1 : 0);
+            body(z * PS + y * SX + GEO::off(s) + q, row * L.RS + lat_slot(s) * L.Qp + q);
+        }
+    };
+    if (!zero)
+        copy([&](int i, int a) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f0[k * N + i] = x[k * len + a];
+        });
+    // this lane's interior items: LDS and global address of x = 4 q (V = 4) or of
+    // the vertex, position of colour 0 (V = 4) or the vertex's colour (V = 1)
+    int qat[QR], gat[QR], rot[QR], qpm[QR];
+    bool qok0[QR];
+    int rid[QR][V];
+#pragma unroll
+    for (int c = 0; c < QR; ++c) {
+        int X, Y, Z;
+        const bool ok = lat_visit_item<V>(g, tid + c * LDS_TPB, &X, &Y, &Z);
+        qat[c] = g.at(X, Y, Z);
+        gat[c] = lat_at(L, X, Y, Z);
+        int P, M;
+        lds_x_offsets<GEO>(X & 3, &P, &M);
+        qpm[c] = P * 65536 + (M & 65535);
+        qok0[c] = X > 0;
+        rot[c] = V == 4 ? (4 * (g.ny + g.nz) - Y - Z) & (S - 1) : (X + Y + Z) & (S - 1);
+        if (!ok) rot[c] |= 64;
+        if (KIND == 1)
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                rid[c][e] = ok ? L.rid[lat_rid_index(L, V == 4 ? X + ((e + rot[c]) & 3) : X, Y, Z)] : 0;
+    }
+    // this lane's surface vertices, dealt from the last wave down; a face's
+    // waves share their class, edges and corners do not (scls < 0)
+    int sat[SR], sga[SR], sPM[SR], sok[SR], srid[SR];
+    int sface[SR], scls[SR];
+#pragma unroll
+    for (int c = 0; c < SR; ++c) {
+        const int wave = c * LDS_WAVES + (LDS_WAVES - 1 - (tid >> 6));
+        int X = 0, Y = 0, Z = 0;
+        const bool ok = lat_rim_lane(g, wave * 64 + (tid & 63), &X, &Y, &Z);
+        sat[c] = g.at(X, Y, Z);
+        sga[c] = lat_at(L, X, Y, Z);
+        srid[c] = L.rid[lat_rid_index(L, X, Y, Z)];
+        int P, M;
+        lds_x_offsets<GEO>(X & 3, &P, &M);
+        sPM[c] = P * 65536 + (M & 65535);
+        scls[c] = lat_class(L, X, Y, Z);
+        // lane 0 of a face's wave is a vertex of the face
+        const bool face = lat_rim_is_face(g, __builtin_amdgcn_readfirstlane(wave));
+        sface[c] = face ? __builtin_amdgcn_readfirstlane(scls[c]) : -1;
+        sok[c] = ok ? 64 | (L.rdir[srid[c]] ? 0 : 128) | ((X + Y + Z) & (S - 1)) << 8 : 0;
+    }
+    __syncthreads();
+    // LDS offset of tap t (global order) from its vertex, whose x +- 1 lie at P, M
+    auto tap = [](int t, int P, int M) __attribute__((always_inline)) -> int {
+        if (t == 0) return 0;
+        const int q = (t - 1) >> 1, m = q == 0 ? 1 : q == 1 ? 2 : q == 2 ? 4 : q == 3 ? 3 : q == 4 ? 6 : q == 5 ? 5 : 7;
+        const bool plus = (t & 1) != 0;
+        return (m & 1 ? (plus ? P : M) : 0) + (plus ? 1 : -1) * ((m & 2 ? SX : 0) + (m & 4 ? PS : 0));
+    };
+#define RIM_PM(c) const int P = sPM[c] >> 16, M = (int)(short)sPM[c]
+    T t3[QR][3][V], s4[QR][V], st[SR][3], ss[SR];
+    // addresses derived from these are formed anew in every pass: hoisted out
+    // of the step loop they would not fit the registers
+    // The constants come from the kernel's arguments again in every pass (more
+    // than the scalar registers hold).
+    const __attribute__((address_space(4))) Lat<T>* C =
+        (const __attribute__((address_space(4))) Lat<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+    auto anew = [&]() __attribute__((always_inline)) {
+        asm volatile("" : "+s"(C));
+#pragma unroll
+        for (int c = 0; c < QR; ++c) asm volatile("" : "+v"(qat[c]), "+v"(rot[c]), "+v"(gat[c]), "+v"(qpm[c]));
+#pragma unroll
+        for (int c = 0; c < SR; ++c) asm volatile("" : "+v"(sat[c]), "+v"(sok[c]), "+v"(sPM[c]), "+v"(scls[c]));
+    };
+    // differences over the opposite pairs at an interior vertex; every load
+    // before the first use (the compiler would wait for each in turn)
+    auto diffs1 = [&](const T* u, int P, int M, T d[7]) __attribute__((always_inline)) {
+        const T v[14] = {u[P],         u[M],          u[SX],         u[-SX],         u[PS],
+                         u[-PS],     u[P + SX],   u[M - SX],     u[SX + PS],   u[-SX - PS],
+                         u[P + PS],  u[M - PS],   u[P + SX + PS], u[M - SX - PS]};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) d[q] = v[2 * q] - v[2 * q + 1];
+    };
+    // rows f - B^T p, by colour; with zero pressure just f
+    auto form_t = [&](bool pz) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < QR; ++c) {
+            if (rot[c] & 64) continue;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int j = 0; j < V; ++j) t3[c][k][j] = b[k * len + gat[c] + lat_sub(j, L.Qp)];
+            if (V == 1) {
+                if (!pz) {
+                    const int P = qpm[c] >> 16, M = (int)(short)qpm[c];
+                    T d[7];
+                    diffs1(pr + qat[c], P, M, d);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+#pragma unroll
+                        for (int q = 0; q < 7; ++q) t3[c][k][0] -= C->bt[k][q] * d[q];
+                }
+            } else {
+                if (!pz) {
+                    LdsRows<T> R;
+                    lds_rows<GEO, 0>(pr + qat[c], R);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) lds_diff<0>(R, -C->bt[k][0], T(0), t3[c][k]);
+                    lds_rows<GEO, 1>(pr + qat[c], R);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) lds_diff<1>(R, -C->bt[k][1], -C->bt[k][3], t3[c][k]);
+                    lds_rows<GEO, 2>(pr + qat[c], R);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) lds_diff<2>(R, -C->bt[k][2], -C->bt[k][5], t3[c][k]);
+                    lds_rows<GEO, 3>(pr + qat[c], R);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) lds_diff<3>(R, -C->bt[k][4], -C->bt[k][6], t3[c][k]);
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) lat_rotate(t3[c][k], rot[c]);
+            }
+        }
+        if (rim) {
+#pragma unroll
+            for (int c = 0; c < SR; ++c) {
+                if (!(sok[c] & 128)) continue;
+                RIM_PM(c);
+                const T* cr = L.cls + (size_t)scls[c] * LC_SIZE + LC_BT;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) st[c][k] = b[k * len + sga[c]];
+                if (!pz)
+#pragma unroll 3
+                    for (int t = 0; t < 15; ++t) {
+                        const T v = pr[sat[c] + tap(t, P, M)];
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) st[c][k] -= cr[15 * k + t] * v;
+                    }
+            }
+        }
+    };
+    // the vertices of colour col of interior item c: body(e, LDS offset, offsets of x +- 1)
+    auto of_colour = [&](int c, int col, auto body) __attribute__((always_inline)) {
+        if (V == 1) {
+            if (rot[c] == col) body(0, qat[c], qpm[c] >> 16, (int)(short)qpm[c]);
+            return;
+        }
+        if (rot[c] & 64) return;
+#pragma unroll
+        for (int e = col; e < V; e += S) {
+            const int j = (e + rot[c]) & 3;
+            if (j == 0 && !qok0[c]) continue;
+            int P, M;
+            lds_x_offsets<GEO>(j, &P, &M);
+            body(e, qat[c] + GEO::off(j), P, M);
+        }
+    };
+    auto vel = [&](auto colc) __attribute__((always_inline)) {
+        constexpr int col = decltype(colc)::value;
+#pragma unroll
+        for (int c = 0; c < QR; ++c)
+            of_colour(c, col, [&](int e, int at, int P, int M) __attribute__((always_inline)) {
+                T w[6], inv;
+                if (KIND == 0) {
+                    inv = C->inva;
+                } else {
+                    const T* ra = L.axr + (size_t)rid[c][e] * LX_SIZE;
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) w[q] = ra[LX_A + q];
+                    inv = ra[LX_INVA];
+                }
+                T v[3], n[3][6];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const T* u = f0 + k * N + at;
+                    n[k][0] = u[P];
+                    n[k][1] = u[M];
+                    n[k][2] = u[SX];
+                    n[k][3] = u[-SX];
+                    n[k][4] = u[PS];
+                    n[k][5] = u[-PS];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (KIND == 0)
+                        v[k] = t3[c][k][e] - C->a[0] * (n[k][0] + n[k][1]) - C->a[1] * (n[k][2] + n[k][3]) -
+                               C->a[2] * (n[k][4] + n[k][5]);
+                    else
+                        v[k] = t3[c][k][e] - w[0] * n[k][0] - w[1] * n[k][1] - w[2] * n[k][2] - w[3] * n[k][3] -
+                               w[4] * n[k][4] - w[5] * n[k][5];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) f0[k * N + at] = v[k] * inv;
+            });
+        if (rim) {
+#pragma unroll
+            for (int c = 0; c < SR; ++c) {
+                if (!(sok[c] & 128) || (sok[c] >> 8) != col) continue;
+                RIM_PM(c);
+                const T* ra = L.axr + (size_t)srid[c] * LX_SIZE;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    T v = st[c][k], n[6];
+#pragma unroll
+                    for (int t = 0; t < 6; ++t) n[t] = f0[k * N + sat[c] + tap(t + 1, P, M)];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int t = 0; t < 6; ++t) v -= ra[LX_A + t] * n[t];
+                    f0[k * N + sat[c]] = v * ra[LX_INVA];
+                }
+            }
+        }
+        __syncthreads();
+    };
+    // (C p) at a vertex of an interior item
+    auto cp_item = [&](int c, int e, int at, int P, int M, T* inv) __attribute__((always_inline)) -> T {
+        const T* p = pr + at;
+        const T n[7] = {p[0], p[P], p[M], p[SX], p[-SX], p[PS], p[-PS]};
+        if (KIND == 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            *inv = C->invc;
+            return C->c0 * n[0] + C->c[0] * (n[1] + n[2]) + C->c[1] * (n[3] + n[4]) + C->c[2] * (n[5] + n[6]);
+        }
+        const T* ra = L.axr + (size_t)rid[c][e] * LX_SIZE;
+        const T w[8] = {ra[LX_C0], ra[LX_C], ra[LX_C + 1], ra[LX_C + 2], ra[LX_C + 3], ra[LX_C + 4], ra[LX_C + 5],
+                        ra[LX_INVC]};
+        __builtin_amdgcn_sched_barrier(0);
+        *inv = w[7];
+        return w[0] * n[0] + w[1] * n[1] + w[2] * n[2] + w[3] * n[3] + w[4] * n[4] + w[5] * n[5] + w[6] * n[6];
+    };
+    // (C p) at surface vertex c
+    auto cp_rim = [&](int c, T* inv) __attribute__((always_inline)) -> T {
+        RIM_PM(c);
+        const T* ra = L.axr + (size_t)srid[c] * LX_SIZE;
+        T w[8], n[7];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) w[t] = ra[LX_C + t];   // the six taps, the centre, 1 / centre
+#pragma unroll
+        for (int t = 0; t < 7; ++t) n[t] = pr[sat[c] + tap(t, P, M)];
+        __builtin_amdgcn_sched_barrier(0);
+        *inv = w[7];
+        T cp = w[6] * n[0];
+#pragma unroll
+        for (int t = 0; t < 6; ++t) cp += w[t] * n[t + 1];
+        return cp;
+    };
+    auto pres = [&](auto colc) __attribute__((always_inline)) {
+        constexpr int col = decltype(colc)::value;
+#pragma unroll
+        for (int c = 0; c < QR; ++c)
+            of_colour(c, col, [&](int e, int at, int P, int M) __attribute__((always_inline)) {
+                T inv;
+                const T cp = cp_item(c, e, at, P, M, &inv);
+                pr[at] += omega * (s4[c][e] - cp) * inv;
+            });
+#pragma unroll
+        for (int c = 0; c < SR; ++c) {
+            if (!(sok[c] & 64) || (sok[c] >> 8) != col) continue;
+            T inv;
+            const T cp = cp_rim(c, &inv);
+            pr[sat[c]] += omega * (ss[c] - cp) * inv;
+        }
+        __syncthreads();
+    };
+    // rows B u - g
+    auto form_s = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < QR; ++c) {
+            if (rot[c] & 64) continue;
+#pragma unroll
+            for (int j = 0; j < V; ++j) s4[c][j] = -b[3 * len + gat[c] + lat_sub(j, L.Qp)];
+            if (V == 1) {
+                const int P = qpm[c] >> 16, M = (int)(short)qpm[c];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    T d[7], e = T(0);
+                    diffs1(f0 + k * N + qat[c], P, M, d);
+#pragma unroll
+                    for (int q = 0; q < 7; ++q) e += C->bt[k][q] * d[q];
+                    s4[c][0] -= e;
+                }
+                continue;
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                LdsRows<T> R;
+                lds_rows<GEO, 0>(f0 + k * N + qat[c], R);
+                lds_diff<0>(R, -C->bt[k][0], T(0), s4[c]);
+                lds_rows<GEO, 1>(f0 + k * N + qat[c], R);
+                lds_diff<1>(R, -C->bt[k][1], -C->bt[k][3], s4[c]);
+                lds_rows<GEO, 2>(f0 + k * N + qat[c], R);
+                lds_diff<2>(R, -C->bt[k][2], -C->bt[k][5], s4[c]);
+                lds_rows<GEO, 3>(f0 + k * N + qat[c], R);
+                lds_diff<3>(R, -C->bt[k][4], -C->bt[k][6], s4[c]);
+            }
+            lat_rotate(s4[c], rot[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < SR; ++c) {
+            RIM_PM(c);
+            T s = T(0);
+            if (sok[c] & 64) s = -b[3 * len + sga[c]];
+            if (sface[c] >= 0) {
+                LatConst<T> cr = (LatConst<T>)(L.cls + (size_t)sface[c] * LC_SIZE + LC_B);
+#pragma unroll 1
+                for (int k = 0; k < 3; ++k) {
+                    T n[15];
+#pragma unroll
+                    for (int t = 0; t < 15; ++t) n[t] = f0[k * N + sat[c] + tap(t, P, M)];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int t = 0; t < 15; ++t) s += cr[15 * k + t] * n[t];
+                }
+            } else if (sok[c] & 64) {
+                const T* cr = L.cls + (size_t)scls[c] * LC_SIZE + LC_B;
+                // fifteen coefficients in flight
+#pragma unroll 1
+                for (int k = 0; k < 3; ++k) {
+                    T w[15], n[15];
+#pragma unroll
+                    for (int t = 0; t < 15; ++t) w[t] = cr[15 * k + t];
+#pragma unroll
+                    for (int t = 0; t < 15; ++t) n[t] = f0[k * N + sat[c] + tap(t, P, M)];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int t = 0; t < 15; ++t) s += w[t] * n[t];
+                }
+            }
+            ss[c] = s;
+        }
+    };
+    using std::integral_constant;
+#pragma unroll 1
+    for (int it = 0; it < steps; ++it)
+#pragma unroll 1
+        for (int i = 0; i < prog.n; ++i) {
+            anew();
+            switch (prog.op[i]) {
+                case LOP_T: form_t(zero && it == 0); break;
+                case LOP_S: form_s(); break;
+                case LOP_V: vel(integral_constant<int, 0>{}); break;
+                case LOP_V + 1: vel(integral_constant<int, 1>{}); break;
+                case LOP_P: pres(integral_constant<int, 0>{}); break;
+                case LOP_P + 1: pres(integral_constant<int, 1>{}); break;
+                default:
+                    if constexpr (S == 4) {
+                        if (prog.op[i] == LOP_V + 2) vel(integral_constant<int, 2>{});
+                        else if (prog.op[i] == LOP_V + 3) vel(integral_constant<int, 3>{});
+                        else if (prog.op[i] == LOP_P + 2) pres(integral_constant<int, 2>{});
+                        else pres(integral_constant<int, 3>{});
+                    }
+            }
+        }
+    if (res) {
+        // r = b - K x: the rows of the steps' functions, by colour position
+        anew();
+        form_t(false);
+        anew();
+        form_s();
+        anew();
+#pragma unroll
+        for (int c = 0; c < QR; ++c)
+#pragma unroll
+            for (int col = 0; col < S; ++col)
+                of_colour(c, col, [&](int e, int at, int P, int M) __attribute__((always_inline)) {
+                    const int j = (e + rot[c]) & 3, a = gat[c] + (V == 4 ? lat_sub(j, L.Qp) : 0);
+                    const T* ra = KIND == 1 ? L.axr + (size_t)rid[c][e] * LX_SIZE : nullptr;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const T* u = f0 + k * N + at;
+                        T v = t3[c][k][e];
+                        if (KIND == 0)
+                            v -= C->a0 * u[0] + C->a[0] * (u[P] + u[M]) + C->a[1] * (u[SX] + u[-SX]) +
+                                 C->a[2] * (u[PS] + u[-PS]);
+                        else
+                            v -= ra[LX_A0] * u[0] + ra[LX_A] * u[P] + ra[LX_A + 1] * u[M] +
+                                 ra[LX_A + 2] * u[SX] + ra[LX_A + 3] * u[-SX] + ra[LX_A + 4] * u[PS] +
+                                 ra[LX_A + 5] * u[-PS];
+                        r[k * len + a] = v;
+                    }
+                    T inv;
+                    r[3 * len + a] = cp_item(c, e, at, P, M, &inv) - s4[c][e];
+                });
+#pragma unroll
+        for (int c = 0; c < SR; ++c) {
+            if (!(sok[c] & 64)) continue;
+            T inv;
+            RIM_PM(c);
+            r[3 * len + sga[c]] = cp_rim(c, &inv) - ss[c];
+            const T* ra = L.axr + (size_t)srid[c] * LX_SIZE;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                T v = T(0);
+                if (sok[c] & 128) {
+                    v = st[c][k] - ra[LX_A0] * f0[k * N + sat[c]];
+#pragma unroll
+                    for (int t = 1; t < 7; ++t) v -= ra[LX_A + t - 1] * f0[k * N + sat[c] + tap(t, P, M)];
+                }
+                r[k * len + sga[c]] = v;
+            }
+        }
+    }
+    // steps end with a barrier
+    copy([&](int i, int a) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k * len + a] = f0[k * N + i];
+    });
+#undef RIM_PM
 }
 
 }  // namespace hhg
