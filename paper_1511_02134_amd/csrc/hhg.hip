@@ -140,6 +140,9 @@ struct hhg_ctx {
     std::vector<LatLevel> G;
     std::vector<Lat<double>> G64;
     std::vector<Lat<float>> G32;
+    uint8_t* lat_owned = nullptr;  // finest level: 1 on vertices (padding 0)
+    double* lat_pinv = nullptr;    // and the pressure preconditioner
+    double* lkv[KV_N] = {};        // Krylov vectors in the lattice layout, or null
     CoarseDev cdl{};               // cd with the level-0 tables of the lattice layout
     double lbytes_vel[4] = {0, 0, 0, 0};   // algorithmic bytes of a velocity colour launch
     size_t coarse_smem = 0;
@@ -442,6 +445,11 @@ size_t layout(hhg_ctx* c, char* ws) {
                              (Y == h.lat[1] - 1 ? 8 : 0) | (X == 0 ? 16 : 0) | (X == h.lat[0] - 1 ? 32 : 0);
             }
         }
+        {
+            const size_t len = lat_geometry<double>(c, c->L).len;
+            c->lat_owned = cv.take<uint8_t>(len);
+            c->lat_pinv = cv.take<double>(len);
+        }
         for (int l = 0; l < nl; ++l) {
             LatLevel& g = c->G[l];
             const Lat<double> G = lat_geometry<double>(c, l);
@@ -470,9 +478,21 @@ size_t layout(hhg_ctx* c, char* ws) {
                 g.b32 = cv.take<float>(v4);
                 g.r32 = cv.take<float>(v4);
             }
-            maxblocks = std::max(maxblocks, lat_grid(lat_quad_lanes(G), G.nz - 2, lat_bs(G)).total +
+            maxblocks = std::max(maxblocks, lat_grid(lat_quad_lanes(G), G.ny - 2, G.nz - 2, lat_bs(G)).total +
                                                 lat_sblocks(g.sfull, lat_bs(G)));
             maxblocks = std::max(maxblocks, ((G.Qi + 1) * G.ny + 255) / 256 * G.nz);
+        }
+    }
+    // the lattice's Krylov vectors share the memory of the per-macro ones: the
+    // ten vectors are contiguous up to their alignment, one more is b64
+    for (int q = 0; q < KV_N; ++q) c->lkv[q] = nullptr;
+    if (lat && c->opts.krylov && lat_applies(c)) {
+        const size_t v4 = 4 * lat_geometry<double>(c, c->L).len;
+        double* base = c->kv[0];
+        const size_t room = (size_t)(c->kv[KV_N - 1] - base) + 4 * (size_t)c->H[c->L].len;
+        if ((KV_N - 1) * v4 <= room && base) {
+            for (int q = 0; q < KV_N - 1; ++q) c->lkv[q] = base + q * v4;
+            c->lkv[KV_N - 1] = c->G[c->L].b64;
         }
     }
     c->npartials = maxblocks;
@@ -600,6 +620,24 @@ hhg_status upload_lattice(hhg_ctx* c) {
         if (m.nu != c->mi.macros[0].nu) c->lat_kind = 1;
     c->G64.assign(c->L + 1, Lat<double>{});
     c->G32.assign(c->L + 1, Lat<float>{});
+    {
+        const HostLevel& h = c->H[c->L];
+        const Lat<double> G = lat_geometry<double>(c, c->L);
+        std::vector<uint8_t> own(c->opts.krylov ? G.len : 0, 0);
+        std::vector<double> pinv(own.size(), 0.0);
+        if (!own.empty())
+            for (int64_t v = 0; v < h.N; ++v) {
+                const int row = (int)(v / G.nx), a = lat_at(G, (int)(v % G.nx), row % G.ny, row / G.ny);
+                const int32_t sid = h.node_sid[v];
+                const double* st = sid < 0 ? &h.st_vol_global[(size_t)(-sid - 1) * ST_SIZE]
+                                           : &h.st[(size_t)sid * ST_SIZE];
+                own[a] = 1;
+                pinv[a] = 1.0 / st[ST_MASSNU];
+            }
+        hhg_status s;
+        if ((s = upload<uint8_t>(c, c->lat_owned, own.data(), own.size())) != HHG_OK) return s;
+        if ((s = upload<double>(c, c->lat_pinv, pinv.data(), pinv.size())) != HHG_OK) return s;
+    }
     for (int l = 0; l <= c->L; ++l) {
         const HostLevel& h = c->H[l];
         LatLevel& g = c->G[l];
@@ -1713,7 +1751,7 @@ template <typename T>
 void lat_vel(hhg_ctx* c, int l, int col, bool pz, int cls, T* x, const T* b, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const bool rb = c->opts.ordering == 2;
-    const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.nz - 2, lat_bs(v.G));
+    const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
     const int sb = lat_sblocks(v.g.svel, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     ops(c, l, rb ? 0.5 : 0.25, 0, 0, 0);
@@ -1738,7 +1776,7 @@ template <typename T>
 void lat_pres(hhg_ctx* c, int l, int col, T* x, const T* sx, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const bool rb = c->opts.ordering == 2;
-    const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.nz - 2, lat_bs(v.G));
+    const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
     const int sb = lat_sblocks(v.g.spres, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     T* p = x + 3 * v.G.len;
@@ -1760,7 +1798,7 @@ template <typename T>
 void lat_bp(hhg_ctx* c, int l, T* x, const T* b, T* sx, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const bool rb = c->opts.ordering == 2;
-    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.nz - 2, lat_bs(v.G));
+    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
     const int sb = lat_sblocks(v.g.sfull, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     const T om = (T)c->opts.omega;
@@ -1827,24 +1865,24 @@ template <typename T>
 inline int lat_visit_of(const LatLevel& g) { return sizeof(T) == 8 ? g.visit64 : g.visit32; }
 
 template <typename T, int KIND, int S, typename GEO, int V, int QR, int SR>
-hipError_t lat_visit_launch(hhg_ctx* c, int l, const T* b, T* x, T* r, int steps, bool zero, bool res, const LatProg& prog,
-                            hipStream_t s, bool setup) {
+hipError_t lat_visit_launch(hhg_ctx* c, int l, const T* b, T* x, T* r, int steps, bool zero, bool res,
+                            const LatProg& prog, hipStream_t s, bool setup, bool vo) {
     if (setup)
         return hipFuncSetAttribute((const void*)k_lat_visit<T, KIND, S, GEO, V, QR, SR>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lat_lds);
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const size_t lds = sizeof(T) * GEO{v.G.nx, v.G.ny, v.G.nz}.values();
     hipLaunchKernelGGL((k_lat_visit<T, KIND, S, GEO, V, QR, SR>), dim3(1), dim3(LDS_TPB), lds, s, v.G, b, x, r, steps,
-                       zero ? 1 : 0, v.g.svel.beg[6] > 0 ? 1 : 0, res ? 1 : 0, prog,
+                       zero ? 1 : 0, v.g.svel.beg[6] > 0 ? 1 : 0, res ? 1 : 0, vo ? 1 : 0, prog,
                        (T)c->opts.omega);
     return hipSuccess;
 }
 template <typename T>
 hipError_t lat_visit_any(hhg_ctx* c, int l, int lanes, const T* b, T* x, T* r, int steps, bool zero, bool res,
-                         const LatProg& prog, hipStream_t s, bool setup) {
+                         const LatProg& prog, hipStream_t s, bool setup, bool vo = false) {
     const bool rb = c->opts.ordering == 2;
 #define LAT_VISIT(K, S, ...) \
-    lat_visit_launch<T, K, S, __VA_ARGS__>(c, l, b, x, r, steps, zero, res, prog, s, setup)
+    lat_visit_launch<T, K, S, __VA_ARGS__>(c, l, b, x, r, steps, zero, res, prog, s, setup, vo)
 #define LAT_VISITS(...)                                                                            \
     do {                                                                                           \
         if (c->lat_kind == 0) return rb ? LAT_VISIT(0, 2, __VA_ARGS__) : LAT_VISIT(0, 4, __VA_ARGS__); \
@@ -1950,7 +1988,7 @@ void lat_visit(hhg_ctx* c, int l, T* x, const T* b, T* r, int steps, bool zero, 
 template <typename T>
 void lat_residual(hhg_ctx* c, int l, const T* x, const T* b, T* r, double* out, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
-    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.nz - 2, lat_bs(v.G));
+    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
     const int sb = lat_sblocks(v.g.sfull, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     ops(c, l, 1, 2, 1, 0);
@@ -1988,11 +2026,21 @@ void lat_project(hhg_ctx* c, int l, T* x, hipStream_t s) {
                        c->inv_mass[l]);
 }
 
-template <typename T, bool SET>
+template <typename T, bool SET, int NF = 4>
 void lat_prolong(hhg_ctx* c, int l, const T* ec, T* xf, hipStream_t s) {
     const LatVecs<T> f = lat_vecs<T>(c, l), v = lat_vecs<T>(c, l - 1);
-    hipLaunchKernelGGL((k_lat_prolong<T, SET>), dim3(((f.G.Qi + 1) * f.G.ny + 255) / 256, f.G.nz), dim3(256), 0,
+    hipLaunchKernelGGL((k_lat_prolong<T, SET, NF>), dim3(((f.G.Qi + 1) * f.G.ny + 255) / 256, f.G.nz), dim3(256), 0,
                        s, f.G, v.G, ec, xf);
+}
+
+// level l - 1's right-hand side from r on level l, its iterate set to 0
+template <typename T, int NF = 4>
+void lat_restrict(hhg_ctx* c, int l, const T* r, hipStream_t s) {
+    const LatVecs<T> v = lat_vecs<T>(c, l), w = lat_vecs<T>(c, l - 1);
+    const LatGrid tg = lat_grid(lat_quad_lanes(w.G), w.G.ny - 2, w.G.nz - 2, lat_bs(w.G));
+    const int sb = lat_sblocks(w.g.sfull, tg.bs);
+    hipLaunchKernelGGL((k_lat_restrict<T, NF>), dim3(sb + tg.total), dim3(tg.bs), 0, s, w.G, v.G, w.g.sfull, sb,
+                       tg, r, w.b, w.x);
 }
 
 // vcycle on the lattice path (l >= 1).  zero: x = 0 on entry; given: as in
@@ -2017,10 +2065,7 @@ void lat_vcycle(hhg_ctx* c, int l, int top, T* x, const T* b, hipStream_t s, boo
     const LatVecs<T> w = lat_vecs<T>(c, l - 1);
     {
         PhaseTimed pt(c, PH_TRANSFER, l, s);
-        const LatGrid tg = lat_grid(lat_quad_lanes(w.G), w.G.nz - 2, lat_bs(w.G));
-        const int sb = lat_sblocks(w.g.sfull, tg.bs);
-        hipLaunchKernelGGL(k_lat_restrict<T>, dim3(sb + tg.total), dim3(tg.bs), 0, s, w.G, v.G,
-                           w.g.sfull, sb, tg, (const T*)v.r, w.b, w.x);
+        lat_restrict<T>(c, l, v.r, s);
     }
     if (l == 1) {
         PhaseTimed pt(c, PH_COARSE, 0, s);
@@ -2060,12 +2105,15 @@ void lat_out(hhg_ctx* c, int l, const double* x, double* v, hipStream_t s) {
 // exactly on level 0.  Works on fields 0..2 of x and b; field 3 of x is left
 // alone.  The mirror of x is current on entry and kept so.
 template <typename T>
-void coarse_avel(hhg_ctx* c, const T* b, T* x, hipStream_t s) {
-    const size_t len = (size_t)c->H[0].len;
+void coarse_avel(hhg_ctx* c, const T* b, T* x, hipStream_t s, const CoarseDev& cd, size_t len) {
     const int rows = (3 * c->cd.nfv + TPB / 64 - 1) / (TPB / 64);
     const int grid = std::max(std::max(rows, (c->cd.N + TPB - 1) / TPB), 1);
-    hipLaunchKernelGGL(k_coarse_avel<T>, dim3(grid), dim3(TPB), 3 * c->cd.nfv * sizeof(double), s,
-                       c->cd, b, len, x, len);
+    hipLaunchKernelGGL(k_coarse_avel<T>, dim3(grid), dim3(TPB), 3 * cd.nfv * sizeof(double), s, cd, b, len, x,
+                       len);
+}
+template <typename T>
+void coarse_avel(hhg_ctx* c, const T* b, T* x, hipStream_t s) {
+    coarse_avel<T>(c, b, x, s, c->cd, (size_t)c->H[0].len);
 }
 
 // velocity fields of x <- 0, with their mirror entries
@@ -2104,6 +2152,66 @@ void vel_cycle(hhg_ctx* c, int l, int nu1, int nu2, T* x, const T* b, hipStream_
         for (int col = 3; col >= 0; --col) colour_pass<T>(c, l, col, true, x, b, s);
 }
 
+// vel_cycle on the lattice path (l >= 1, colour order); zero: the velocity of x
+// is 0 on entry
+void lat_vel_cycle(hhg_ctx* c, int l, int nu1, int nu2, double* x, const double* b, hipStream_t s, bool zero) {
+    const LatVecs<double> v = lat_vecs<double>(c, l), w = lat_vecs<double>(c, l - 1);
+    // a visit's fixed cost (its level in and out of the LDS) is that of four
+    // launches: quad visits (17^3 vertices, one step 23 us; launches 17) need
+    // two steps
+    const int lanes = v.g.visit64 > 1 && nu1 + nu2 < 4 ? 0 : v.g.visit64;
+    LatProg down{}, up{};
+    for (LatProg* p : {&down, &up}) p->op[p->n++] = LOP_T;
+    for (int col = 0; col < 4; ++col) {
+        down.op[down.n++] = (unsigned char)(LOP_V + col);
+        up.op[up.n++] = (unsigned char)(LOP_V + 3 - col);
+    }
+    if (lanes) {
+        ops(c, l, nu1 + 1.0, 0, 0, 0);
+        (void)lat_visit_any<double>(c, l, lanes, b, x, v.r, nu1, zero, true, down, s, false, true);
+    } else {
+        for (int q = 0; q < nu1; ++q)
+            for (int col = 0; col < 4; ++col) lat_vel<double>(c, l, col, true, HHG_K_VEL, x, b, s);
+        const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
+        const int sb = lat_sblocks(v.g.sfull, tg.bs);
+        const dim3 grid(sb + tg.total), blk(tg.bs);
+        ops(c, l, 1, 0, 0, 0);
+        if (c->lat_kind)
+            hipLaunchKernelGGL((k_lat_ares<double, 1>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg, b, x, v.r);
+        else
+            hipLaunchKernelGGL((k_lat_ares<double, 0>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg, b, x, v.r);
+    }
+    lat_restrict<double, 3>(c, l, v.r, s);
+    if (l == 1)
+        coarse_avel<double>(c, w.b, w.x, s, c->cdl, w.G.len);
+    else
+        lat_vel_cycle(c, l - 1, nu1, nu2, w.x, w.b, s, true);
+    lat_prolong<double, false, 3>(c, l, w.x, x, s);
+    if (lanes) {
+        ops(c, l, nu2, 0, 0, 0);
+        (void)lat_visit_any<double>(c, l, lanes, b, x, v.r, nu2, false, false, up, s, false, true);
+        return;
+    }
+    for (int q = 0; q < nu2; ++q)
+        for (int col = 3; col >= 0; --col) lat_vel<double>(c, l, col, true, HHG_K_VEL, x, b, s);
+}
+
+// y = K x on the finest level of the lattice path
+void lat_apply(hhg_ctx* c, const double* x, double* y, hipStream_t s) {
+    const int l = c->L;
+    const LatVecs<double> v = lat_vecs<double>(c, l);
+    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
+    const int sb = lat_sblocks(v.g.sfull, tg.bs);
+    const dim3 grid(sb + tg.total), blk(tg.bs);
+    ops(c, l, 1, 2, 1, 0);
+    if (c->lat_kind)
+        hipLaunchKernelGGL((k_lat_res<double, 1, true, false, true>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg,
+                           (const double*)nullptr, x, y, c->partials);
+    else
+        hipLaunchKernelGGL((k_lat_res<double, 0, true, false, true>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg,
+                           (const double*)nullptr, x, y, c->partials);
+}
+
 // ------------------------------------------------------- Krylov helpers
 inline int vgrid(size_t n) {
     return (int)std::max<size_t>(1, std::min<size_t>((n + TPB - 1) / TPB, VGRID_MAX));
@@ -2116,24 +2224,32 @@ void vreduce(hhg_ctx* c, size_t len, double* out, bool sqrt_out, hipStream_t s) 
 }
 
 // <a, b> over owned slots of the finest level, fields 0..nf-1 -> *out
-void vdot(hhg_ctx* c, const double* a, const double* b, int nf, double* out, hipStream_t s) {
-    const size_t len = (size_t)c->H[c->L].len;
-    hipLaunchKernelGGL(k_vdot, dim3(vgrid(len)), dim3(TPB), 0, s, a, b, c->A[c->L].owned, len, nf,
-                       c->kpart);
+void vdot(hhg_ctx* c, const double* a, const double* b, int nf, double* out, hipStream_t s,
+          bool lat = false) {
+    const size_t len = lat ? c->G64[c->L].len : (size_t)c->H[c->L].len;
+    hipLaunchKernelGGL(k_vdot, dim3(vgrid(len)), dim3(TPB), 0, s, a, b,
+                       (const uint8_t*)(lat ? c->lat_owned : c->A[c->L].owned), len, nf, c->kpart);
     vreduce(c, len, out, false, s);
 }
 
 // z = diag(Ahat, Shat)^-1 v on the finest level (eq. precond_block_diag):
 // one velocity V(nu, nu) cycle from zero and the weighted lumped mass; *vz
 // receives <v, z>
-void block_prec(hhg_ctx* c, int nu, const double* v, double* z, double* vz, hipStream_t s) {
+void block_prec(hhg_ctx* c, int nu, const double* v, double* z, double* vz, hipStream_t s,
+                bool lat = false) {
     const int L = c->L;
-    const size_t len = (size_t)c->H[L].len;
-    fill_velocity<double>(c, L, z, s);
-    vel_cycle<double>(c, L, nu, nu, z, v, s);
+    const size_t len = lat ? c->G64[L].len : (size_t)c->H[L].len;
+    if (lat) {
+        fill<double>(z, 3 * len, 0.0, s);
+        lat_vel_cycle(c, L, nu, nu, z, v, s, true);
+    } else {
+        fill_velocity<double>(c, L, z, s);
+        vel_cycle<double>(c, L, nu, nu, z, v, s);
+    }
     ops(c, L, 0, 0, 0, 1);
-    hipLaunchKernelGGL(k_mr_precp_dot, dim3(vgrid(len)), dim3(TPB), 0, s, v, z, c->A[L].pinv,
-                       c->A[L].owned, len, c->kpart);
+    hipLaunchKernelGGL(k_mr_precp_dot, dim3(vgrid(len)), dim3(TPB), 0, s, v, z,
+                       (const double*)(lat ? c->lat_pinv : c->A[L].pinv),
+                       (const uint8_t*)(lat ? c->lat_owned : c->A[L].owned), len, c->kpart);
     vreduce(c, len, vz, false, s);
 }
 
@@ -2971,7 +3087,7 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
     const int bs = lat_bs(G);
     for (int per : {lat_pair_lanes(G, 1), lat_pair_lanes(G, 2), lat_quad_lanes(G)})
         for (int order = 0; order < 3 && per > 0; ++order) {
-            const LatGrid tg = lat_grid(per, planes, bs);
+            const LatGrid tg = lat_grid(per, G.ny - 2, planes, bs);
             std::vector<int> hit((size_t)tg.per * planes, 0), slot(tg.total, 0);
             for (int v = 0; v < tg.total; ++v) {
                 const LatTile T = lat_tile(tg, planes, v, order);
@@ -2987,7 +3103,7 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
     for (int NC = 1; NC <= 2; ++NC)
         for (int col = 0; col < (NC == 2 ? 2 : 4) && l > 0; ++col) {
             std::vector<uint8_t> seen(N, 0);
-            const LatGrid tg = lat_grid(lat_pair_lanes(G, NC), planes, bs);
+            const LatGrid tg = lat_grid(lat_pair_lanes(G, NC), G.ny - 2, planes, bs);
             for (int v = 0; v < tg.total; ++v)
                 for (int lane = 0; lane < bs; ++lane) {
                     const LatTile t = lat_tile(tg, planes, v, c->opts.block_order);
@@ -3032,7 +3148,7 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
         }
     // quads: windows and the restriction into this level
     std::vector<uint8_t> seen(N, 0);
-    const LatGrid qg = lat_grid(lat_quad_lanes(G), planes, bs);
+    const LatGrid qg = lat_grid(lat_quad_lanes(G), G.ny - 2, planes, bs);
     for (int v = 0; v < qg.total; ++v)
         for (int lane = 0; lane < bs; ++lane) {
             const LatTile t = lat_tile(qg, planes, v, c->opts.block_order);
@@ -3505,27 +3621,42 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
     if (!(rtol >= 0.0) || maxit < 0 || maxit > 100000 || nu < 1 || nu > 16)
         return fail(c, HHG_EINVAL, "need rtol >= 0, 0 <= maxit <= 100000, 1 <= nu <= 16");
     hipStream_t s = (hipStream_t)stream;
-    double* x = (double*)xv;
-    const double* b = (const double*)bv;
+    double* const xc = (double*)xv;   // the caller's vectors
+    const double* const bc = (const double*)bv;
+    // Kuhn meshes: every vector in the lattice layout, x and b converted once
+    const bool lat = c->lkv[0] != nullptr;
+    double* x = lat ? c->G[c->L].x64 : xc;
     hhg_solve_info loc;
     hhg_solve_info* I = info ? info : &loc;
     std::memset(I, 0, sizeof(*I));
     reset_ops(c);
     const int L = c->L;
-    const size_t len = (size_t)c->H[L].len, n4 = 4 * len;
-    double* R = c->kv[0];
-    double* Vb[2] = {c->kv[1], c->kv[2]};
-    double* Zb[2] = {c->kv[3], c->kv[4]};
-    double* Q = c->kv[5];
-    double* Wb[2] = {c->kv[6], c->kv[7]};
-    double* KWb[2] = {c->kv[8], c->kv[9]};
-    for (int q = 0; q < KV_N; ++q) fill<double>(c->kv[q], n4, 0.0, s);
+    const size_t len = lat ? c->G64[L].len : (size_t)c->H[L].len, n4 = 4 * len;
+    double* const* kv = lat ? c->lkv : c->kv;
+    const uint8_t* owned = lat ? c->lat_owned : c->A[L].owned;
+    double* R = kv[0];
+    double* Vb[2] = {kv[1], kv[2]};
+    double* Zb[2] = {kv[3], kv[4]};
+    double* Q = kv[5];
+    double* Wb[2] = {kv[6], kv[7]};
+    double* KWb[2] = {kv[8], kv[9]};
     hipEvent_t e0 = next_event(c), e1 = next_event(c);
     if (e0) (void)hipEventRecord(e0, s);
+    // on the lattice kv[9] is b's vector until the first residual is formed
+    for (int q = 0; q < (lat ? KV_N - 1 : KV_N); ++q) fill<double>(kv[q], n4, 0.0, s);
+    if (lat) {
+        lat_in(c, L, xc, x, s);
+        lat_in(c, L, bc, kv[KV_N - 1], s);
+    }
     // r_0 = f~ - K x_0, V_1 = r_0, Z_1 = P^-1 r_0 (unnormalised Lanczos vectors)
-    residual_norm<double>(c, L, x, b, R, c->kscal + 2, s);
+    if (lat) {
+        lat_residual<double>(c, L, x, kv[KV_N - 1], R, c->kscal + 2, s);
+        fill<double>(kv[KV_N - 1], n4, 0.0, s);
+    } else {
+        residual_norm<double>(c, L, x, bc, R, c->kscal + 2, s);
+    }
     hipLaunchKernelGGL(k_copy, dim3(vgrid(n4)), dim3(TPB), 0, s, Vb[1], (const double*)R, n4);
-    block_prec(c, nu, Vb[1], Zb[0], c->kscal + 1, s);
+    block_prec(c, nu, Vb[1], Zb[0], c->kscal + 1, s, lat);
     double h[3];
     hhg_status rs = read_scalars(c, h, c->kscal, 3, s);
     if (rs != HHG_OK) return rs;
@@ -3545,12 +3676,15 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
     while (st == HHG_ENOCONV && beta > 0.0) {
         if (it >= maxit) break;
         // Lanczos: Q = K Z_j, alpha_j = <Q, Z_j> / beta_j^2, V_{j+1}, Z_{j+1} = P^-1 V_{j+1}
-        full_pass<double, MODE_APPLY>(c, L, Zb[zc], nullptr, Q, s);
-        vdot(c, Q, Zb[zc], 4, c->kscal + 0, s);
+        if (lat)
+            lat_apply(c, Zb[zc], Q, s);
+        else
+            full_pass<double, MODE_APPLY>(c, L, Zb[zc], nullptr, Q, s);
+        vdot(c, Q, Zb[zc], 4, c->kscal + 0, s, lat);
         hipLaunchKernelGGL(k_mr_lanczos, dim3(vgrid(n4)), dim3(TPB), 0, s, (const double*)Q,
                            (const double*)Vb[cur], Vb[cur ^ 1], n4, beta,
                            it == 0 ? 0.0 : beta / beta_prev, (const double*)c->kscal);
-        block_prec(c, nu, Vb[cur ^ 1], Zb[zc ^ 1], c->kscal + 1, s);
+        block_prec(c, nu, Vb[cur ^ 1], Zb[zc ^ 1], c->kscal + 1, s, lat);
         if ((rs = read_scalars(c, h, c->kscal, 3, s)) != HHG_OK) return rs;
         if (pending) {
             // residual of the previous update (Q, V and Z do not touch x or r)
@@ -3583,7 +3717,7 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
         MrCoef k{1.0 / (beta * gamma), eps / gamma, delta / gamma, tau};
         hipLaunchKernelGGL(k_mr_update, dim3(vgrid(len)), dim3(TPB), 0, s, (const double*)Zb[zc],
                            Wb[wc], (const double*)Wb[wc ^ 1], x, (const double*)Q, KWb[wc],
-                           (const double*)KWb[wc ^ 1], R, (const uint8_t*)c->A[L].owned, len, k,
+                           (const double*)KWb[wc ^ 1], R, owned, len, k,
                            c->kpart);
         vreduce(c, len, c->kscal + 2, true, s);
         pending = true;
@@ -3606,7 +3740,12 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
         else if (h[0] <= rtol * r0)
             st = HHG_OK;
     }
-    project<double>(c, L, x, s);
+    if (lat) {
+        lat_project<double>(c, L, x, s);
+        lat_out(c, L, x, xc, s);
+    } else {
+        project<double>(c, L, x, s);
+    }
     if (e1) (void)hipEventRecord(e1, s);
     I->t_solve_ms = event_ms(e0, e1);
     if (I->cycles > 0 && I->rel_res > 0.0) I->rho_mean = std::pow(I->rel_res, 1.0 / I->cycles);

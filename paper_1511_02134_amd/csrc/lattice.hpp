@@ -107,17 +107,21 @@ __host__ __device__ __forceinline__ int lat_div(int item, float inv) {
 // vertices, FP64): plane by plane the velocity sweep fetched twice its bytes.
 struct LatGrid {
     int per, G, NG, ZB, total, bs;
+    float inv_zg, inv_g, inv_row;   // 1 / (ZB G), 1 / G, 1 / (lanes of a row)
 };
 // lanes: row lanes of a plane
-__host__ __device__ __forceinline__ LatGrid lat_grid(int lanes, int planes, int bs) {
+__host__ __device__ __forceinline__ LatGrid lat_grid(int lanes, int rows, int planes, int bs) {
     LatGrid g;
     const int per = (lanes + bs - 1) / bs;
+    g.inv_row = (float)rows / (float)lanes;
     g.bs = bs;
     g.per = per;
     g.NG = (per + 7) / 8;
     g.G = (per + g.NG - 1) / g.NG;
     g.ZB = (planes + 7) / 8;
     g.total = 8 * g.NG * g.ZB * g.G;
+    g.inv_zg = 1.0f / (float)(g.ZB * g.G);
+    g.inv_g = 1.0f / (float)g.G;
     return g;
 }
 struct LatTile {
@@ -126,11 +130,19 @@ struct LatTile {
     bool ok;
 };
 __host__ __device__ __forceinline__ LatTile lat_tile(const LatGrid& g, int planes, int v, int order) {
-    const int slab = g.NG * g.ZB * g.G;
+    const int zg = g.ZB * g.G, slab = g.NG * zg;
     LatTile T;
-    T.t = order == 2 ? g.total - 1 - v : order == 0 ? v : (v & 7) * slab + (v >> 3);
-    const int zb = T.t / slab, i = T.t - zb * slab, zg = g.ZB * g.G;
-    const int gp = i / zg, r = i - gp * zg, zi = r / g.G;
+    int zb, i;
+    if (order == 1) {
+        zb = v & 7;
+        i = v >> 3;
+        T.t = zb * slab + i;
+    } else {
+        T.t = order == 2 ? g.total - 1 - v : v;
+        zb = T.t / slab;
+        i = T.t - zb * slab;
+    }
+    const int gp = lat_div(i, g.inv_zg), r = i - gp * zg, zi = lat_div(r, g.inv_g);
     T.z = zb * g.ZB + zi;
     T.part = gp * g.G + (r - zi * g.G);
     T.ok = T.z < planes && T.part < g.per;
@@ -154,7 +166,7 @@ __host__ __device__ __forceinline__ LatPair lat_pair_lane(const Lat<T>& L, int c
     LatPair P;
     const int half = L.Qi >> 1, lpr = NC * half;
     const int item = tile.part * tg.bs + lane;
-    const int row = lat_div(item, 1.0f / (float)lpr), li = item - row * lpr;
+    const int row = lat_div(item, tg.inv_row), li = item - row * lpr;
     P.z = tile.z + 1;
     P.y = row + 1;
     P.ok = row < L.ny - 2;
@@ -175,7 +187,7 @@ __host__ __device__ __forceinline__ LatPair lat_quad_lane(const Lat<T>& L, const
                                                           const LatTile& tile, int lane) {
     LatPair P;
     const int item = tile.part * tg.bs + lane;
-    const int row = lat_div(item, 1.0f / (float)L.Qi);
+    const int row = lat_div(item, tg.inv_row);
     P.z = tile.z + 1;
     P.y = row + 1;
     P.s = 0;
@@ -534,11 +546,11 @@ __global__ void __launch_bounds__(256) k_lat_pres(Lat<T> L, LatSurf B, int col, 
 }
 
 // ---------------------------------------------------------------------------
-// r = b - K x (Dirichlet velocity rows 0).  WR: r is stored; NRM: per-block
+// r = b - K x (Dirichlet velocity rows 0); AP: r = K x instead.  WR: r is stored; NRM: per-block
 // partial sums of r^2 at partials[tile] (volume) and partials[total + block]
 // (surface), independent of the workgroup order.
 // ---------------------------------------------------------------------------
-template <typename T, int KIND, bool WR, bool NRM>
+template <typename T, int KIND, bool WR, bool NRM, bool AP = false>
 __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, LatGrid tg,
                                                  const T* __restrict__ b, const T* __restrict__ x,
                                                  T* __restrict__ r, double* __restrict__ partials) {
@@ -555,26 +567,26 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
             const T* __restrict__ rc = L.rec + (size_t)id * LR_SIZE;
             int nb[15];
             lat_taps(L, X, Y, Z, nb);
-            T v = b[3 * len + nb[0]];
+            T v = AP ? T(0) : b[3 * len + nb[0]];
 #pragma unroll
             for (int t = 0; t < 7; ++t) v += rc[LR_C + t] * p[nb[t]];
 #pragma unroll 1
             for (int k = 0; k < 3; ++k)
 #pragma unroll
                 for (int t = 0; t < 15; ++t) v -= rc[LR_B + 15 * k + t] * x[k * len + nb[t]];
-            if (WR) r[3 * len + nb[0]] = v;
+            if (WR) r[3 * len + nb[0]] = AP ? -v : v;
             if (NRM) acc += (double)v * (double)v;
             const bool dir = L.rdir[id] != 0;
 #pragma unroll 1
             for (int k = 0; k < 3; ++k) {
                 T w = T(0);
                 if (!dir) {
-                    w = b[k * len + nb[0]];
+                    w = AP ? T(0) : b[k * len + nb[0]];
 #pragma unroll
                     for (int t = 0; t < 15; ++t) w -= rc[LR_BT + 15 * k + t] * p[nb[t]];
                     for (int t = 0; t < 7; ++t) w -= rc[LR_A + t] * x[k * len + nb[t]];
                 }
-                if (WR) r[k * len + nb[0]] = w;
+                if (WR) r[k * len + nb[0]] = AP ? -w : w;
                 if (NRM) acc += (double)w * (double)w;
             }
         }
@@ -632,7 +644,7 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
                                                  ra[j][LX_A + 4] * za + ra[j][LX_A + 5] * zb;
                     const int a = at + lat_sub(j, Qp);
                     const T bt = k == 0 ? t[0][j] : k == 1 ? t[1][j] : t[2][j];
-                    const T v = ld1(b + k * len, a) - bt - au;
+                    const T v = AP ? bt + au : ld1(b + k * len, a) - bt - au;
                     if (j > 0 || first) {
                         if (WR) st1(r + k * len, a, v);
                         if (NRM) acc += (double)v * (double)v;
@@ -642,7 +654,7 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int a = at + lat_sub(j, Qp);
-                const T v = ld1(b + 3 * len, a) + rp[j];
+                const T v = AP ? -rp[j] : ld1(b + 3 * len, a) + rp[j];
                 if (j > 0 || first) {
                     if (WR) st1(r + 3 * len, a, v);
                     if (NRM) acc += (double)v * (double)v;
@@ -656,12 +668,72 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
     }
 }
 
+// t_k = b_k - (A u)_k (k = 0..2; Dirichlet rows 0): the velocity residual of the
+// velocity multigrid.
+template <typename T, int KIND>
+__global__ void __launch_bounds__(256) k_lat_ares(Lat<T> L, LatSurf B, int sb, LatGrid tg,
+                                                  const T* __restrict__ b, const T* __restrict__ x,
+                                                  T* __restrict__ r) {
+    const size_t len = L.len;
+    if ((int)blockIdx.x < sb) {
+        int X, Y, Z;
+        if (!lat_surf_lane(L, B, 1, 0, (int)blockIdx.x * tg.bs + (int)threadIdx.x, &X, &Y, &Z)) return;
+        const int id = L.rid[lat_rid_index(L, X, Y, Z)];
+        const T* __restrict__ rc = L.rec + (size_t)id * LR_SIZE;
+        const bool dir = L.rdir[id] != 0;
+        int nb[15];
+        lat_taps(L, X, Y, Z, nb);
+        for (int k = 0; k < 3; ++k) {
+            T w = T(0);
+            if (!dir) {
+                w = b[k * len + nb[0]];
+#pragma unroll
+                for (int t = 0; t < 7; ++t) w -= rc[LR_A + t] * x[k * len + nb[t]];
+            }
+            r[k * len + nb[0]] = w;
+        }
+        return;
+    }
+    const LatTile tile = lat_tile(tg, L.nz - 2, (int)blockIdx.x - sb, L.order);
+    if (!tile.ok) return;
+    const LatPair P = lat_quad_lane(L, tg, tile, threadIdx.x);
+    if (!P.ok) return;
+    const int at = (P.z * L.ny + P.y) * L.RS + P.q, Qp = L.Qp;
+    const T* ra[4];
+    if (KIND == 1)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            ra[j] = L.axr + (size_t)L.rid[lat_rid_index(L, 4 * P.q + j, P.y, P.z)] * LX_SIZE;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const T* __restrict__ u = x + k * len;
+        T c[6];   // x = 4q - 1 .. 4q + 4
+        c[1] = ld1(u, at);
+        c[2] = ld1(u, at + 2 * Qp);
+        c[3] = ld1(u, at + Qp);
+        c[4] = ld1(u, at + 3 * Qp);
+        c[5] = ld1(u, at + 1);
+        c[0] = ld1(u, at + 3 * Qp - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int a = at + lat_sub(j, Qp);
+            const T ya = ld1(u, a + L.RS), yb = ld1(u, a - L.RS), za = ld1(u, a + L.ZS), zb = ld1(u, a - L.ZS);
+            const T au = KIND == 0 ? L.a0 * c[j + 1] + L.a[0] * (c[j + 2] + c[j]) + L.a[1] * (ya + yb) + L.a[2] * (za + zb)
+                                   : ra[j][LX_A0] * c[j + 1] + ra[j][LX_A] * c[j + 2] + ra[j][LX_A + 1] * c[j] +
+                                         ra[j][LX_A + 2] * ya + ra[j][LX_A + 3] * yb + ra[j][LX_A + 4] * za +
+                                         ra[j][LX_A + 5] * zb;
+            const T v = ld1(b + k * len, a) - au;
+            if (j > 0 || P.q > 0) st1(r + k * len, a, v);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Restriction bc = P^T rf (weights 1 and 1/2, Dirichlet velocity rows 0), with
 // the coarse iterate xc set to 0 in the same pass.  Interior lanes: the coarse
 // quad q reads the fine row segments 8 q - 1 .. 8 q + 7 as pairs.
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, int NF = 4>
 __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSurf B, int sb, LatGrid tg,
                                                       const T* __restrict__ rf, T* __restrict__ bc,
                                                       T* __restrict__ xc) {
@@ -673,7 +745,7 @@ __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSur
         const int a = lat_at(C, X, Y, Z);
         int nb[15];
         lat_taps(F, 2 * X, 2 * Y, 2 * Z, nb);
-        for (int f = 0; f < 4; ++f) {
+        for (int f = 0; f < NF; ++f) {
             T acc = T(0);
             if (f == 3 || !dir) {
 #pragma unroll
@@ -693,7 +765,7 @@ __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSur
     const int at = (P.z * C.ny + P.y) * C.RS + P.q;
     const int fa = (2 * P.z * F.ny + 2 * P.y) * F.RS + 2 * P.q;
 #pragma unroll 1
-    for (int f = 0; f < 4; ++f) {
+    for (int f = 0; f < NF; ++f) {
         const T* __restrict__ v = rf + f * lf;
         T acc[4], ctr[4];
 #pragma unroll
@@ -731,7 +803,7 @@ __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSur
 // Prolongation over every fine vertex: x_f += P e_c (SET: x_f = P e_c except on
 // Dirichlet velocity).  A fine vertex with odd bits d is the midpoint of the
 // coarse vertices (X - d) / 2 and (X + d) / 2.
-template <typename T, bool SET>
+template <typename T, bool SET, int NF = 4>
 __global__ void __launch_bounds__(256) k_lat_prolong(Lat<T> F, Lat<T> C, const T* __restrict__ ec,
                                                      T* __restrict__ xf) {
     const size_t lc = C.len, lf = F.len;
@@ -755,9 +827,9 @@ __global__ void __launch_bounds__(256) k_lat_prolong(Lat<T> F, Lat<T> C, const T
             if (x < F.nx && (x == 0 || x == F.nx - 1 || y == 0 || y == F.ny - 1 || z == 0 || z == F.nz - 1))
                 keep[j] = F.rdir[F.rid[lat_rid_index(F, x, y, z)]] != 0;
         }
-    T e[4][4], xv[4][4];
+    T e[NF][4], xv[NF][4];
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
+    for (int f = 0; f < NF; ++f) {
         const T* __restrict__ c = ec + f * lc;
         const T l0 = ld1(c, lo + i0), l1 = ld1(c, lo + i1), h0 = ld1(c, hi + i0), h1 = ld1(c, hi + i1),
                 h2 = ld1(c, hi + i2);
@@ -769,7 +841,7 @@ __global__ void __launch_bounds__(256) k_lat_prolong(Lat<T> F, Lat<T> C, const T
         for (int j = 0; j < 4; ++j) xv[f][j] = ld1(xf + f * lf, at + lat_sub(j, F.Qp));
     }
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (j > 0 && last) continue;
@@ -861,6 +933,9 @@ struct LdsGeom {
     __host__ __device__ bool holds() const { return nx <= SX_ && ny <= SY_; }
 };
 
+// i / d for small i and d
+__host__ __device__ __forceinline__ int lat_idiv(int i, int d) { return (int)(((float)i + 0.5f) / (float)d); }
+
 // Surface lane i of a visit: faces z0, z1, y0, y1, x0, x1 without their edges,
 // each padded to whole waves, then edges and corners.
 template <typename G>
@@ -882,7 +957,7 @@ __host__ __device__ __forceinline__ bool lat_rim_lane(const G& g, int i, int* x,
     if (f < 6) {
         const int a = f < 4 ? g.nx - 2 : g.ny - 2, b = f < 2 ? g.ny - 2 : g.nz - 2;
         if (k >= a * b) return false;
-        const int r = k / a, s = k - r * a;
+        const int r = lat_idiv(k, a), s = k - r * a;
         *x = f < 4 ? s + 1 : f == 4 ? 0 : g.nx - 1;
         *y = f < 2 ? r + 1 : f == 2 ? 0 : f == 3 ? g.ny - 1 : s + 1;
         *z = f == 0 ? 0 : f == 1 ? g.nz - 1 : r + 1;
@@ -930,8 +1005,8 @@ __host__ __device__ __forceinline__ bool lat_rim_is_face(const G& g, int w) {
 // fall into distinct banks.
 template <int V, typename G>
 __host__ __device__ __forceinline__ bool lat_visit_item(const G& g, int i, int* x, int* y, int* z) {
-    const int w = V == 4 ? (g.nx - 1) / 4 : g.nx - 2, row = i / w, h = g.ny - 2;
-    const int zz = row / h, yy = row - zz * h;
+    const int w = V == 4 ? (g.nx - 1) / 4 : g.nx - 2, row = lat_idiv(i, w), h = g.ny - 2;
+    const int zz = lat_idiv(row, h), yy = row - zz * h;
     const bool ok = zz < g.nz - 2;
     // yy counts 0, 4, 8, .., 1, 5, 9, ..
     int r = yy, c = 0;
@@ -1024,11 +1099,12 @@ constexpr int LDS_WAVES = 16, LDS_TPB = 64 * LDS_WAVES;
 // interior vertices: more waves share the latency); QR, SR: interior items and
 // surface vertices per lane (at most).  S = 2: red-black, 4: colours.  zero: x =
 // 0 on entry; rim: some surface vertex has a free velocity; res: r = b - K x
-// after the last step.  prog: the passes of a step.
+// after the last step.  prog: the passes of a step.  vo: the
+// velocity block alone (A u = b, fields 0..2; field 3 is left alone).
 template <typename T, int KIND, int S, typename GEO, int V, int QR, int SR>
 __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __restrict__ b,
                                                        T* __restrict__ x, T* __restrict__ r, int steps,
-                                                       int zero, int rim, int res, LatProg prog, T omega) {
+                                                       int zero, int rim, int res, int vo, LatProg prog, T omega) {
     extern __shared__ char lds_raw[];
     const size_t len = L.len;
     const GEO g{L.nx, L.ny, L.nz};
@@ -1041,15 +1117,16 @@ __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __rest
     // whole rows in and out
     auto copy = [&](auto body) __attribute__((always_inline)) {
         for (int i = tid; i < g.nx * g.ny * g.nz; i += LDS_TPB) {
-            const int row = i / g.nx, e = i - row * g.nx, z = row / g.ny, y = row - z * g.ny;
-            const int s = e <= L.Qi ? 0 : (e - 1) / L.Qi, q = e - s * L.Qi - (s > 0 ? 1 : 0);
+            const int row = lat_idiv(i, g.nx), e = i - row * g.nx, z = lat_idiv(row, g.ny), y = row - z * g.ny;
+            const int s = e <= L.Qi ? 0 : e <= 2 * L.Qi ? 1 : e <= 3 * L.Qi ? 2 : 3, q = e - s * L.Qi - (s > 0 ? 1 : 0);
             body(z * PS + y * SX + GEO::off(s) + q, row * L.RS + lat_slot(s) * L.Qp + q);
         }
     };
     if (!zero)
         copy([&](int i, int a) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) f0[k * N + i] = x[k * len + a];
+            for (int k = 0; k < 4; ++k)
+                if (k < 3 || !vo) f0[k * N + i] = x[k * len + a];
         });
     // this lane's interior items: LDS and global address of x = 4 q (V = 4) or of
     // the vertex, position of colour 0 (V = 4) or the vertex's colour (V = 1)
@@ -1381,7 +1458,7 @@ __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __rest
         for (int i = 0; i < prog.n; ++i) {
             anew();
             switch (prog.op[i]) {
-                case LOP_T: form_t(zero && it == 0); break;
+                case LOP_T: form_t(vo || (zero && it == 0)); break;
                 case LOP_S: form_s(); break;
                 case LOP_V: vel(integral_constant<int, 0>{}); break;
                 case LOP_V + 1: vel(integral_constant<int, 1>{}); break;
@@ -1399,9 +1476,9 @@ __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __rest
     if (res) {
         // r = b - K x: the rows of the steps' functions, by colour position
         anew();
-        form_t(false);
+        form_t(vo != 0);
         anew();
-        form_s();
+        if (!vo) form_s();
         anew();
 #pragma unroll
         for (int c = 0; c < QR; ++c)
@@ -1423,6 +1500,7 @@ __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __rest
                                  ra[LX_A + 5] * u[-PS];
                         r[k * len + a] = v;
                     }
+                    if (vo) return;
                     T inv;
                     r[3 * len + a] = cp_item(c, e, at, P, M, &inv) - s4[c][e];
                 });
@@ -1431,7 +1509,7 @@ __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __rest
             if (!(sok[c] & 64)) continue;
             T inv;
             RIM_PM(c);
-            r[3 * len + sga[c]] = cp_rim(c, &inv) - ss[c];
+            if (!vo) r[3 * len + sga[c]] = cp_rim(c, &inv) - ss[c];
             const T* ra = L.axr + (size_t)srid[c] * LX_SIZE;
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
@@ -1448,7 +1526,8 @@ __global__ void __launch_bounds__(LDS_TPB) k_lat_visit(Lat<T> L, const T* __rest
     // steps end with a barrier
     copy([&](int i, int a) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x[k * len + a] = f0[k * N + i];
+        for (int k = 0; k < 4; ++k)
+            if (k < 3 || !vo) x[k * len + a] = f0[k * N + i];
     });
 #undef RIM_PM
 }

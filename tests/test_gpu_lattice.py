@@ -135,3 +135,81 @@ def test_lattice_solve_after_viscosity_change(ordering):
         a = s.solve(xs, s.rhs(fi), rtol=1e-8)
         c = t.solve(xt, t.rhs(fi), rtol=1e-8)
         assert a["res_hist"] == c["res_hist"] and torch.equal(xs, xt)
+
+
+@pytest.mark.parametrize("ext,R,nu_max,outflow", [((1, 1, 1), 3, 1.0, False), ((1, 1, 1), 5, 1.0, True),
+                                                  ((3, 1, 2), 4, 4.0, False), ((1, 1, 1), 6, 3.0, False)])
+def test_lattice_pminres_is_minres(ext, R, nu_max, outflow):
+    """Preconditioned MINRES on the lattice: the first iterates minimise the
+    residual norm of the preconditioner over the Krylov space spanned with
+    hhg_apply and hhg_vel_cycle (per-macro layout).  The minimisation in double
+    loses the square of the basis' condition, so the iterates agree to 1e-7."""
+    import paper_1511_02134_amd as P
+    print(f"[gpu-case] lattice pminres {ext} R={R}", flush=True)
+    mesh = _box(ext, nu_max, outflow)
+    s = P.Solver(*mesh, R, krylov=1)
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    f = torch.randn(3, s.num_nodes(), generator=gen, dtype=torch.float64, device="cuda")
+    b = s.rhs(s.scatter(f))
+    x0 = s.scatter(torch.randn(4, s.num_nodes(), generator=gen, dtype=torch.float64, device="cuda"))
+    _, dmask = s.node_info()
+    free = torch.ones(4, s.num_nodes(), dtype=torch.float64, device="cuda")
+    free[:3, torch.tensor(dmask, device="cuda")] = 0.0
+    ijk, _ = s.node_info()
+    # lumped pressure mass over 1/nu: sum over the tetrahedra around a vertex of |T| / (4 nu_T)
+    pm = torch.zeros(s.num_nodes(), dtype=torch.float64)
+    n = 1 << R
+    lat = [e * n + 1 for e in ext]
+    for t in range(len(mesh[1])):
+        v0 = mesh[0][mesh[1][t][0]].astype(int) * n
+        ax = [int(np.argmax(mesh[0][mesh[1][t][q + 1]] - mesh[0][mesh[1][t][q]])) for q in range(3)]
+        c = np.stack(np.meshgrid(*[np.arange(n)] * 3, indexing="ij"), -1).reshape(-1, 3)
+        for s6 in itertools.permutations(range(3)):
+            path = [np.zeros(3, int)]
+            for q in s6:
+                path.append(path[-1] + np.eye(3, dtype=int)[q])
+            cen = c + sum(path) / 4
+            inside = (cen[:, ax[0]] > cen[:, ax[1]]) & (cen[:, ax[1]] > cen[:, ax[2]])
+            for p in path:
+                X = v0 + c[inside] + p
+                pm.index_add_(0, torch.from_numpy(X[:, 0] + lat[0] * (X[:, 1] + lat[1] * X[:, 2])),
+                              torch.full((len(X),), (1 / n) ** 3 / 24 / mesh[2][t], dtype=torch.float64))
+    pm = pm.to("cuda")
+
+    def K(v):
+        return s.gather(s.apply(s.scatter(v)))
+
+    def prec(v):
+        z = s.vector()
+        s.vel_cycle(z, s.scatter(v))
+        z = s.gather(z)
+        z[3] = v[3] / pm
+        return z
+
+    r, nrm = s.residual(x0, b)
+    v = s.gather(r)
+    zs = [prec(v)]
+    its = 3
+    for _ in range(its - 1):
+        q = prec(K(zs[-1]))
+        for z in zs:
+            q = q - (q * z).sum() / (z * z).sum() * z
+        zs.append(q)
+    zs = [z / z.norm() for z in zs]
+    # min |v - sum y_i K z_i| in the norm of the preconditioner
+    A = [K(z) for z in zs]
+    PA = [prec(a) for a in A]
+    G = torch.stack([torch.stack([(a * p).sum() for p in PA]) for a in A])
+    h = torch.stack([(v * p).sum() for p in PA])
+    y = torch.linalg.solve(0.5 * (G + G.T), h)
+    ref = s.gather(x0) + sum(c * z for c, z in zip(y, zs))
+    xs = x0.clone()
+    info = s.pminres(xs, b, rtol=0.0, maxit=its)
+    got = s.gather(xs)
+    if not outflow:
+        ref[3] -= (torch.tensor(s.mass_weights(), device="cuda") * ref[3]).sum() / float(np.prod(ext))
+    d = s.gather(x0)
+    assert info["r0"] == pytest.approx(nrm, rel=1e-12)
+    assert float((got - ref).abs().max() / (ref - d).abs().max()) <= 1e-7
+    _, end = s.residual(xs, b)
+    assert info["r_final"] == pytest.approx(end, rel=1e-9)
