@@ -105,7 +105,7 @@ struct LatLevel {
     double *rec64 = nullptr, *axr64 = nullptr, *x64 = nullptr, *b64 = nullptr, *r64 = nullptr;
     float *rec32 = nullptr, *axr32 = nullptr, *x32 = nullptr, *b32 = nullptr, *r32 = nullptr;
     int nrec = 0, nrid = 0;
-    LatSurf svel, spres, sfull;   // surface lanes of velocity, pressure and full launches
+    LatSurf svel, spres, sring;   // surface lanes of velocity, pressure and full launches
     // one-workgroup visits (k_lat_visit): 0 no, otherwise the variant
     int visit64 = 0, visit32 = 0;
 };
@@ -312,6 +312,23 @@ bool lat_applies(const hhg_ctx* c) {
     return lat_reserved(c) && c->opts.op == 0 && c->opts.ordering != 1;
 }
 
+// full launches: quads of every interior row, and the rows' ends
+template <typename T>
+LatGrid lat_quad_grid(const Lat<T>& G) {
+    return lat_grid(lat_quad_lanes(G), G.ny - 2, G.nz - 2, lat_bs(G), 2);
+}
+// launches of 2 x 2 rows, side 8: with the rows' ends
+template <typename T>
+LatGrid lat_block_grid(const Lat<T>& G, int side) {
+    return lat_grid(lat_block_lanes(G), G.ny / 2, G.nz / 2, 256, side);
+}
+// Levels that take the kernels of 2 x 2 rows: one viscosity and eight workgroups
+// for each of the 256 CUs
+template <typename T>
+bool lat_blocks(const hhg_ctx* c, const Lat<T>& G) {
+    return c->lat_kind == 0 && lat_block_lanes(G) / 256 * (G.nz / 2) >= 2048;
+}
+
 LatSurf lat_surface(const Lat<double>& G, int S, int faces) {
     LatSurf B;
     B.beg[0] = 0;
@@ -456,7 +473,7 @@ size_t layout(hhg_ctx* c, char* ws) {
             const int S = c->opts.ordering == 2 ? 2 : 4;
             g.svel = lat_surface(G, S, vel_faces);
             g.spres = lat_surface(G, S, 63);
-            g.sfull = lat_surface(G, 1, 63);
+            g.sring = lat_surface(G, 1, 15);
             g.nrec = c->H[l].nm + (int)c->H[l].keys.size();
             g.nrid = (c->mi.ext[0] + 1) * (c->mi.ext[1] + 1) * (c->mi.ext[2] + 1) * LPAT;
             g.rid = cv.take<int>(g.nrid);
@@ -478,8 +495,8 @@ size_t layout(hhg_ctx* c, char* ws) {
                 g.b32 = cv.take<float>(v4);
                 g.r32 = cv.take<float>(v4);
             }
-            maxblocks = std::max(maxblocks, lat_grid(lat_quad_lanes(G), G.ny - 2, G.nz - 2, lat_bs(G)).total +
-                                                lat_sblocks(g.sfull, lat_bs(G)));
+            maxblocks = std::max(maxblocks, lat_quad_grid(G).total +
+                                                lat_sblocks(g.sring, lat_bs(G)));
             maxblocks = std::max(maxblocks, ((G.Qi + 1) * G.ny + 255) / 256 * G.nz);
         }
     }
@@ -1756,6 +1773,20 @@ void lat_vel(hhg_ctx* c, int l, int col, bool pz, int cls, T* x, const T* b, hip
     const dim3 grid(sb + tg.total), blk(tg.bs);
     ops(c, l, rb ? 0.5 : 0.25, 0, 0, 0);
     Timed tm(c, cls, s, l == c->L, rb ? c->lbytes_vel[col] + c->lbytes_vel[col + 2] : c->lbytes_vel[col]);
+    if (rb && lat_blocks(c, v.G)) {
+        const LatGrid bg = lat_block_grid(v.G, 0);
+        const int bsb = lat_sblocks(v.g.svel, bg.bs);
+        const dim3 g2(bsb + bg.total), b2(bg.bs);
+        if (col == 0 && pz)
+            hipLaunchKernelGGL((k_lat_vel_blk<T, 0, true>), g2, b2, 0, s, v.G, v.g.svel, bsb, bg, b, x);
+        else if (col == 0)
+            hipLaunchKernelGGL((k_lat_vel_blk<T, 0, false>), g2, b2, 0, s, v.G, v.g.svel, bsb, bg, b, x);
+        else if (pz)
+            hipLaunchKernelGGL((k_lat_vel_blk<T, 1, true>), g2, b2, 0, s, v.G, v.g.svel, bsb, bg, b, x);
+        else
+            hipLaunchKernelGGL((k_lat_vel_blk<T, 1, false>), g2, b2, 0, s, v.G, v.g.svel, bsb, bg, b, x);
+        return;
+    }
 #define LAT_VEL(K, NC, PZ) \
     hipLaunchKernelGGL((k_lat_vel<T, K, NC, PZ>), grid, blk, 0, s, v.G, v.g.svel, col, sb, tg, b, x)
     const int sel = (c->lat_kind ? 4 : 0) + (rb ? 2 : 0) + (pz ? 1 : 0);
@@ -1798,21 +1829,28 @@ template <typename T>
 void lat_bp(hhg_ctx* c, int l, T* x, const T* b, T* sx, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const bool rb = c->opts.ordering == 2;
-    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
-    const int sb = lat_sblocks(v.g.sfull, tg.bs);
+    const LatGrid tg = lat_quad_grid(v.G);
+    const int sb = lat_sblocks(v.g.sring, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     const T om = (T)c->opts.omega;
     const int all = c->opts.p_sweep;
     ops(c, l, 0, 1, rb ? 0.5 : 0.25, 0);
     Timed tm(c, HHG_K_APPLY, s, l == c->L, c->bytes_bp_fused[rb ? 4 : 0]);
+    if (rb && lat_blocks(c, v.G)) {
+        const LatGrid bg = lat_block_grid(v.G, 8);
+        const int bsb = lat_sblocks(v.g.sring, bg.bs);
+        hipLaunchKernelGGL(k_lat_bp_blk<T>, dim3(bsb + bg.total), dim3(bg.bs), 0, s, v.G, v.g.sring, bsb, bg, b, x,
+                           sx, om, all);
+        return;
+    }
     if (c->lat_kind == 0 && rb)
-        hipLaunchKernelGGL((k_lat_bp<T, 0, 2>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+        hipLaunchKernelGGL((k_lat_bp<T, 0, 2>), grid, blk, 0, s, v.G, v.g.sring, 0, sb, tg, b, x, sx, om, all);
     else if (c->lat_kind == 0)
-        hipLaunchKernelGGL((k_lat_bp<T, 0, 1>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+        hipLaunchKernelGGL((k_lat_bp<T, 0, 1>), grid, blk, 0, s, v.G, v.g.sring, 0, sb, tg, b, x, sx, om, all);
     else if (rb)
-        hipLaunchKernelGGL((k_lat_bp<T, 1, 2>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+        hipLaunchKernelGGL((k_lat_bp<T, 1, 2>), grid, blk, 0, s, v.G, v.g.sring, 0, sb, tg, b, x, sx, om, all);
     else
-        hipLaunchKernelGGL((k_lat_bp<T, 1, 1>), grid, blk, 0, s, v.G, v.g.sfull, 0, sb, tg, b, x, sx, om, all);
+        hipLaunchKernelGGL((k_lat_bp<T, 1, 1>), grid, blk, 0, s, v.G, v.g.sring, 0, sb, tg, b, x, sx, om, all);
 }
 
 // One inexact Uzawa step (the steps of uzawa_step and uzawa_step_rb).  pz: the
@@ -1988,14 +2026,14 @@ void lat_visit(hhg_ctx* c, int l, T* x, const T* b, T* r, int steps, bool zero, 
 template <typename T>
 void lat_residual(hhg_ctx* c, int l, const T* x, const T* b, T* r, double* out, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l);
-    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
-    const int sb = lat_sblocks(v.g.sfull, tg.bs);
+    const LatGrid tg = lat_quad_grid(v.G);
+    const int sb = lat_sblocks(v.g.sring, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     ops(c, l, 1, 2, 1, 0);
     {
         Timed tm(c, HHG_K_APPLY, s, l == c->L, c->bytes_res);
 #define LAT_RES(K, WR, NRM) \
-    hipLaunchKernelGGL((k_lat_res<T, K, WR, NRM>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg, b, x, r, c->partials)
+    hipLaunchKernelGGL((k_lat_res<T, K, WR, NRM>), grid, blk, 0, s, v.G, v.g.sring, sb, tg, b, x, r, c->partials)
         if (!out) {
             if (c->lat_kind) LAT_RES(1, true, false);
             else LAT_RES(0, true, false);
@@ -2010,7 +2048,7 @@ void lat_residual(hhg_ctx* c, int l, const T* x, const T* b, T* r, double* out, 
     }
     if (out)
         hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(RTPB), 0, s, c->partials,
-                           tg.total + (v.g.sfull.beg[6] + tg.bs - 1) / tg.bs, out, 1);
+                           tg.total + (v.g.sring.beg[6] + tg.bs - 1) / tg.bs, out, 1);
 }
 
 template <typename T>
@@ -2037,9 +2075,9 @@ void lat_prolong(hhg_ctx* c, int l, const T* ec, T* xf, hipStream_t s) {
 template <typename T, int NF = 4>
 void lat_restrict(hhg_ctx* c, int l, const T* r, hipStream_t s) {
     const LatVecs<T> v = lat_vecs<T>(c, l), w = lat_vecs<T>(c, l - 1);
-    const LatGrid tg = lat_grid(lat_quad_lanes(w.G), w.G.ny - 2, w.G.nz - 2, lat_bs(w.G));
-    const int sb = lat_sblocks(w.g.sfull, tg.bs);
-    hipLaunchKernelGGL((k_lat_restrict<T, NF>), dim3(sb + tg.total), dim3(tg.bs), 0, s, w.G, v.G, w.g.sfull, sb,
+    const LatGrid tg = lat_quad_grid(w.G);
+    const int sb = lat_sblocks(w.g.sring, tg.bs);
+    hipLaunchKernelGGL((k_lat_restrict<T, NF>), dim3(sb + tg.total), dim3(tg.bs), 0, s, w.G, v.G, w.g.sring, sb,
                        tg, r, w.b, w.x);
 }
 
@@ -2172,14 +2210,14 @@ void lat_vel_cycle(hhg_ctx* c, int l, int nu1, int nu2, double* x, const double*
     } else {
         for (int q = 0; q < nu1; ++q)
             for (int col = 0; col < 4; ++col) lat_vel<double>(c, l, col, true, HHG_K_VEL, x, b, s);
-        const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
-        const int sb = lat_sblocks(v.g.sfull, tg.bs);
+        const LatGrid tg = lat_quad_grid(v.G);
+        const int sb = lat_sblocks(v.g.sring, tg.bs);
         const dim3 grid(sb + tg.total), blk(tg.bs);
         ops(c, l, 1, 0, 0, 0);
         if (c->lat_kind)
-            hipLaunchKernelGGL((k_lat_ares<double, 1>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg, b, x, v.r);
+            hipLaunchKernelGGL((k_lat_ares<double, 1>), grid, blk, 0, s, v.G, v.g.sring, sb, tg, b, x, v.r);
         else
-            hipLaunchKernelGGL((k_lat_ares<double, 0>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg, b, x, v.r);
+            hipLaunchKernelGGL((k_lat_ares<double, 0>), grid, blk, 0, s, v.G, v.g.sring, sb, tg, b, x, v.r);
     }
     lat_restrict<double, 3>(c, l, v.r, s);
     if (l == 1)
@@ -2200,15 +2238,15 @@ void lat_vel_cycle(hhg_ctx* c, int l, int nu1, int nu2, double* x, const double*
 void lat_apply(hhg_ctx* c, const double* x, double* y, hipStream_t s) {
     const int l = c->L;
     const LatVecs<double> v = lat_vecs<double>(c, l);
-    const LatGrid tg = lat_grid(lat_quad_lanes(v.G), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
-    const int sb = lat_sblocks(v.g.sfull, tg.bs);
+    const LatGrid tg = lat_quad_grid(v.G);
+    const int sb = lat_sblocks(v.g.sring, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     ops(c, l, 1, 2, 1, 0);
     if (c->lat_kind)
-        hipLaunchKernelGGL((k_lat_res<double, 1, true, false, true>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg,
+        hipLaunchKernelGGL((k_lat_res<double, 1, true, false, true>), grid, blk, 0, s, v.G, v.g.sring, sb, tg,
                            (const double*)nullptr, x, y, c->partials);
     else
-        hipLaunchKernelGGL((k_lat_res<double, 0, true, false, true>), grid, blk, 0, s, v.G, v.g.sfull, sb, tg,
+        hipLaunchKernelGGL((k_lat_res<double, 0, true, false, true>), grid, blk, 0, s, v.G, v.g.sring, sb, tg,
                            (const double*)nullptr, x, y, c->partials);
 }
 
@@ -3148,11 +3186,18 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
         }
     // quads: windows and the restriction into this level
     std::vector<uint8_t> seen(N, 0);
-    const LatGrid qg = lat_grid(lat_quad_lanes(G), G.ny - 2, planes, bs);
+    const LatGrid qg = lat_quad_grid(G);
     for (int v = 0; v < qg.total; ++v)
         for (int lane = 0; lane < bs; ++lane) {
             const LatTile t = lat_tile(qg, planes, v, c->opts.block_order);
             if (!t.ok) continue;
+            if (t.end >= 0) {
+                int x, y, z;
+                if (!lat_end_lane(qg, t, G.ny - 2, G.nx, G.ny, G.nz, lane, &x, &y, &z)) continue;
+                CK((x == 0 || x == G.nx - 1) && y >= 1 && y <= G.ny - 2 && z >= 1 && z <= G.nz - 2, "end of a row");
+                CK(!seen[node(x, y, z)]++, "end of a row visited twice");
+                continue;
+            }
             const LatPair P = lat_quad_lane(G, qg, t, lane);
             if (!P.ok) continue;
             CK(P.z >= 1 && P.z <= G.nz - 2 && P.y >= 1 && P.y <= G.ny - 2 && P.q >= 0 && P.q < G.Qi, "quad lane");
@@ -3183,7 +3228,7 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
                            "restriction tap");
             }
         }
-    const LatSurf B = lat_surface(G, 1, 63);
+    const LatSurf B = lat_surface(G, 1, 15);
     for (int i = 0; i < B.beg[6] + 300; ++i) {
         int x, y, z;
         if (!lat_surf_lane(G, B, 1, 0, i, &x, &y, &z)) continue;
@@ -3209,6 +3254,56 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
     if (!check_visit(c, l, Lds17{G.nx, G.ny, G.nz}, err) || !check_visit(c, l, Lds33{G.nx, G.ny, G.nz}, err) ||
         !check_visit(c, l, Lds33w{G.nx, G.ny, G.nz}, err))
         return false;
+    // blocks of 2 x 2 rows
+    if (l > 0) {
+        const LatGrid bg = lat_block_grid(G, 8);
+        std::fill(seen.begin(), seen.end(), 0);
+        for (int v = 0; v < bg.total; ++v) {
+            const LatTile t = lat_tile(bg, G.nz / 2, v, c->opts.block_order);
+            if (!t.ok) continue;
+            for (int lane = 0; lane < bg.bs && t.end >= 0; ++lane) {
+                int x, y, z;
+                if (!lat_end_lane(bg, t, G.ny / 2, G.nx, G.ny, G.nz, lane, &x, &y, &z)) continue;
+                CK((x == 0 || x == G.nx - 1) && y >= 1 && y <= G.ny - 2 && z >= 1 && z <= G.nz - 2, "end of a block's row");
+                CK(!seen[node(x, y, z)]++, "end of a block's row visited twice");
+            }
+            if (t.end >= 0) continue;
+            for (int lane = 0; lane < bg.bs; ++lane) {
+                const LatBlock<double> P = lat_block_lane(G, bg, t, lane);
+                if (!P.ok) continue;
+                CK((P.y0 & 1) && (P.z0 & 1) && P.y0 <= G.ny - 2 && P.z0 <= G.nz - 2 && P.q >= 0 && P.q < G.Qi,
+                   "block lane");
+                for (int dy = -1; dy <= 2; ++dy)
+                    for (int dz = -1; dz <= 2; ++dz) {
+                        const double* f0 = nullptr;
+                        const int64_t a =
+                            ((dz == -1  ? P.template base<0, -1>(G, f0, 0)
+                              : dz == 0 ? P.template base<0, 0>(G, f0, 0)
+                              : dz == 1 ? P.template base<0, 1>(G, f0, 0)
+                                        : P.template base<0, 2>(G, f0, 0)) -
+                             f0) +
+                            (dy == 2 ? (int64_t)P.v2 / 8 : (int64_t)P.v0 / 8 + dy * G.RS);
+                        CK(inside(a, 2) && inside(a + 3 * G.Qp - 1, 2), "block row out of range");
+                        const int y = std::min(P.y0 + dy, G.ny - 1), z = std::min(P.z0 + dz, G.nz - 1);
+                        for (int j = 0; j < 4; ++j) CK(holds(a + lat_sub(j, G.Qp), 4 * P.q + j, y, z), "block row");
+                    }
+                for (int o = 0; o < 4; ++o) {
+                    if (!P.in(G, o & 1, o >> 1)) continue;
+                    const int y = P.y0 + (o & 1), z = P.z0 + (o >> 1);
+                    for (int j = 0; j < 4; ++j) {
+                        const int x = 4 * P.q + j;
+                        if (x == 0) continue;
+                        CK(!surface(x, y, z) && !seen[node(x, y, z)]++, "block vertex");
+                        CK(((j + lat_first(0, o)) & 1) == ((x + y + z) & 1), "block vertex's parity");
+                    }
+                }
+            }
+        }
+        for (int z = 1; z < G.nz - 1; ++z)
+            for (int y = 1; y < G.ny - 1; ++y)
+                for (int x = 0; x < G.nx; ++x)
+                    CK(seen[node(x, y, z)] == 1, "blocks do not cover the rows");
+    }
     // records: vertices with one index share their stencil record
     std::vector<int> sid_of((size_t)g.nrid, INT32_MIN);
     for (int z = 0; z < G.nz; ++z)

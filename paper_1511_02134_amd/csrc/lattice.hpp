@@ -99,6 +99,11 @@ __host__ __device__ __forceinline__ int lat_div(int item, float inv) {
     return (int)(((float)item + 0.5f) * inv);
 }
 
+// smallest r with r d >= item
+__host__ __device__ __forceinline__ int lat_div_up(int item, float inv) {
+    return item <= 0 ? 0 : lat_div(item - 1, inv) + 1;
+}
+
 // Tiles of a volume launch: `per` blocks of bs lanes cover the interior rows of
 // a plane.  The planes are cut into eight slabs of ZB, one per XCD (workgroup b
 // runs on XCD b mod 8); inside a slab, G blocks of a plane (about 2048 lanes)
@@ -107,30 +112,40 @@ __host__ __device__ __forceinline__ int lat_div(int item, float inv) {
 // vertices, FP64): plane by plane the velocity sweep fetched twice its bytes.
 struct LatGrid {
     int per, G, NG, ZB, total, bs;
-    float inv_zg, inv_g, inv_row;   // 1 / (ZB G), 1 / G, 1 / (lanes of a row)
+    int side, SB;                   // lanes per row on the x faces, their blocks in a group
+    float inv_zg, inv_g, inv_row;   // 1 / (ZB (G + SB)), 1 / (G + SB), 1 / (lanes of a row)
 };
-// lanes: row lanes of a plane
-__host__ __device__ __forceinline__ LatGrid lat_grid(int lanes, int rows, int planes, int bs) {
+// lanes: row lanes of a plane; side: lanes per row that also take the row's two
+// ends on the faces x = 0 and x = nx - 1 (0: a launch without them).  These read
+// the lines of the volume rows (a vertex needs one or two entries of each), so
+// they go ahead of the rows of their group, in blocks of their own, and share
+// the lines in L2: as part of the surface lanes the two faces fetched them again.
+__host__ __device__ __forceinline__ LatGrid lat_grid(int lanes, int rows, int planes, int bs, int side = 0, int G = 8) {
     LatGrid g;
     const int per = (lanes + bs - 1) / bs;
     g.inv_row = (float)rows / (float)lanes;
     g.bs = bs;
     g.per = per;
-    g.NG = (per + 7) / 8;
+    g.NG = (per + G - 1) / G;
     g.G = (per + g.NG - 1) / g.NG;
     g.ZB = (planes + 7) / 8;
-    g.total = 8 * g.NG * g.ZB * g.G;
-    g.inv_zg = 1.0f / (float)(g.ZB * g.G);
-    g.inv_g = 1.0f / (float)g.G;
+    const int row = lanes / rows, gl = g.G * bs;
+    const int most = gl % row == 0 ? gl / row : gl / row + 1;   // rows that begin in a group
+    g.side = side;
+    g.SB = ((most < rows ? most : rows) * side + bs - 1) / bs;
+    g.total = 8 * g.NG * g.ZB * (g.G + g.SB);
+    g.inv_zg = 1.0f / (float)(g.ZB * (g.G + g.SB));
+    g.inv_g = 1.0f / (float)(g.G + g.SB);
     return g;
 }
 struct LatTile {
     int t;          // natural index (partial sums)
     int z, part;    // interior plane and block of the plane
+    int end;        // >= 0: block of the x faces beside group `part`
     bool ok;
 };
 __host__ __device__ __forceinline__ LatTile lat_tile(const LatGrid& g, int planes, int v, int order) {
-    const int zg = g.ZB * g.G, slab = g.NG * zg;
+    const int zg = g.ZB * (g.G + g.SB), slab = g.NG * zg;
     LatTile T;
     int zb, i;
     if (order == 1) {
@@ -144,9 +159,28 @@ __host__ __device__ __forceinline__ LatTile lat_tile(const LatGrid& g, int plane
     }
     const int gp = lat_div(i, g.inv_zg), r = i - gp * zg, zi = lat_div(r, g.inv_g);
     T.z = zb * g.ZB + zi;
-    T.part = gp * g.G + (r - zi * g.G);
-    T.ok = T.z < planes && T.part < g.per;
+    const int w = r - zi * (g.G + g.SB);
+    T.end = w < g.SB ? w : -1;
+    T.part = w < g.SB ? gp : gp * g.G + (w - g.SB);
+    T.ok = T.z < planes && (w < g.SB || T.part < g.per);
     return T;
+}
+// vertex of lane idx of the x-face blocks of a group: rows that begin in it, two
+// ends each (side 8: the ends of the four rows of a 2 x 2 block)
+__host__ __device__ __forceinline__ bool lat_end_lane(const LatGrid& g, const LatTile& t, int rows, int nx, int ny,
+                                                      int nz, int lane, int* x, int* y, int* z) {
+    const int idx = t.end * g.bs + lane, lg = g.side == 8 ? 3 : 1, gl = g.G * g.bs;
+    const int row0 = lat_div_up(t.part * gl, g.inv_row), row1 = lat_div_up((t.part + 1) * gl, g.inv_row);
+    const int row = row0 + (idx >> lg);
+    *x = idx & 1 ? nx - 1 : 0;
+    if (g.side == 8) {
+        *y = 2 * row + 1 + (idx >> 1 & 1);
+        *z = 2 * t.z + 1 + (idx >> 2 & 1);
+    } else {
+        *y = row + 1;
+        *z = t.z + 1;
+    }
+    return row < row1 && row < rows && *y <= ny - 2 && *z <= nz - 2;
 }
 
 // Interior row lanes of a colour launch: NC = 2 the parity col (0 or 1) of
@@ -224,6 +258,21 @@ __host__ __device__ __forceinline__ bool lat_surf_lane(const Lat<T>& L, const La
     return *y >= 1 && *y <= L.ny - 2;
 }
 
+// Whether the lane has a vertex of the box's surface: the blocks before the tiles
+// (*tile is left alone) or a tile's x faces; *ok: it has one.  Uniform per block.
+template <typename T>
+__device__ __forceinline__ bool lat_surf_work(const Lat<T>& L, const LatSurf& B, int sb, const LatGrid& tg, int rows,
+                                              int planes, LatTile* tile, bool* ok, int* x, int* y, int* z) {
+    if ((int)blockIdx.x < sb) {
+        *ok = lat_surf_lane(L, B, 1, 0, (int)blockIdx.x * tg.bs + (int)threadIdx.x, x, y, z);
+        return true;
+    }
+    *tile = lat_tile(tg, planes, (int)blockIdx.x - sb, L.order);
+    if (tile->end < 0) return false;
+    *ok = tile->ok && lat_end_lane(tg, *tile, rows, L.nx, L.ny, L.nz, threadIdx.x, x, y, z);
+    return true;
+}
+
 // The 14 neighbour addresses of a surface vertex in the global tap order; a
 // direction that leaves the box gets the vertex itself (its coefficients are 0).
 template <typename T>
@@ -269,6 +318,86 @@ __host__ __device__ __forceinline__ void lat_x_offsets(int s, int Qp, int* P, in
     *M = (lat_slot((s + 3) & 3) - here) * Qp - (s == 0 ? 1 : 0);
 }
 
+// Surface lanes of the passes: whole records, taps by address.
+template <typename T, bool PZ>
+__device__ __forceinline__ void lat_vel_surface(const Lat<T>& L, const LatSurf& B, int S, int col, int idx,
+                                                const T* __restrict__ b, T* __restrict__ x) {
+    const size_t len = L.len;
+    int X, Y, Z;
+    if (!lat_surf_lane(L, B, S, col, idx, &X, &Y, &Z)) return;
+    const int id = L.rid[lat_rid_index(L, X, Y, Z)];
+    if (L.rdir[id]) return;
+    const T* __restrict__ r = L.rec + (size_t)id * LR_SIZE;
+    int nb[15];
+    lat_taps(L, X, Y, Z, nb);
+    for (int k = 0; k < 3; ++k) {
+        T acc = b[k * len + nb[0]];
+        if (!PZ)
+            for (int g = 0; g < 15; ++g) acc -= r[LR_BT + 15 * k + g] * x[3 * len + nb[g]];
+        for (int g = 1; g < 7; ++g) acc -= r[LR_A + g] * x[k * len + nb[g]];
+        x[k * len + nb[0]] = acc * r[LR_INVA];
+    }
+}
+template <typename T>
+__device__ __forceinline__ void lat_bp_surface(const Lat<T>& L, int X, int Y, int Z, int cm, int col,
+                                               const T* __restrict__ g, T* __restrict__ x,
+                                               T* __restrict__ sx, T omega, int all) {
+    const size_t len = L.len;
+    T* __restrict__ p = x + 3 * len;
+    const T* __restrict__ r = L.rec + (size_t)L.rid[lat_rid_index(L, X, Y, Z)] * LR_SIZE;
+    int nb[15];
+    lat_taps(L, X, Y, Z, nb);
+    T s = -g[nb[0]];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int t = 0; t < 15; ++t) s += r[LR_B + 15 * k + t] * x[k * len + nb[t]];
+    if (((X + Y + Z) & cm) == col) {
+        T cp = T(0);
+#pragma unroll
+        for (int t = 0; t < 7; ++t) cp += r[LR_C + t] * p[nb[t]];
+        p[nb[0]] += omega * (s - cp) * r[LR_INVC];
+        if (!all) return;
+    }
+    sx[nb[0]] = s;
+}
+// returns the lane's sum of r^2
+template <typename T, bool WR, bool NRM, bool AP>
+__device__ __forceinline__ double lat_res_surface(const Lat<T>& L, int X, int Y, int Z,
+                                                  const T* __restrict__ b, const T* __restrict__ x,
+                                                  T* __restrict__ r) {
+    const size_t len = L.len;
+    const T* __restrict__ p = x + 3 * len;
+    double acc = 0.0;
+    const int id = L.rid[lat_rid_index(L, X, Y, Z)];
+    const T* __restrict__ rc = L.rec + (size_t)id * LR_SIZE;
+    int nb[15];
+    lat_taps(L, X, Y, Z, nb);
+    T v = AP ? T(0) : b[3 * len + nb[0]];
+#pragma unroll
+    for (int t = 0; t < 7; ++t) v += rc[LR_C + t] * p[nb[t]];
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int t = 0; t < 15; ++t) v -= rc[LR_B + 15 * k + t] * x[k * len + nb[t]];
+    if (WR) r[3 * len + nb[0]] = AP ? -v : v;
+    if (NRM) acc += (double)v * (double)v;
+    const bool dir = L.rdir[id] != 0;
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        T w = T(0);
+        if (!dir) {
+            w = AP ? T(0) : b[k * len + nb[0]];
+#pragma unroll
+            for (int t = 0; t < 15; ++t) w -= rc[LR_BT + 15 * k + t] * p[nb[t]];
+            for (int t = 0; t < 7; ++t) w -= rc[LR_A + t] * x[k * len + nb[t]];
+        }
+        if (WR) r[k * len + nb[0]] = AP ? -w : w;
+        if (NRM) acc += (double)w * (double)w;
+    }
+    return acc;
+}
+
 // ---------------------------------------------------------------------------
 // Velocity sweep of one parity or colour (Section 3.5): u_k <- (f_k - (B^T p)_k
 // - sum A u_k) / A_xx.  The B^T p rows are formed on the fly from p instead of
@@ -282,20 +411,7 @@ __global__ void __launch_bounds__(256) k_lat_vel(Lat<T> L, LatSurf B, int col, i
     const size_t len = L.len;
     const T* __restrict__ p = x + 3 * len;
     if ((int)blockIdx.x < sb) {
-        int X, Y, Z;
-        if (!lat_surf_lane(L, B, 4 / NC, col, (int)blockIdx.x * tg.bs + (int)threadIdx.x, &X, &Y, &Z)) return;
-        const int id = L.rid[lat_rid_index(L, X, Y, Z)];
-        if (L.rdir[id]) return;
-        const T* __restrict__ r = L.rec + (size_t)id * LR_SIZE;
-        int nb[15];
-        lat_taps(L, X, Y, Z, nb);
-        for (int k = 0; k < 3; ++k) {
-            T acc = b[k * len + nb[0]];
-            if (!PZ)
-                for (int g = 0; g < 15; ++g) acc -= r[LR_BT + 15 * k + g] * p[nb[g]];
-            for (int g = 1; g < 7; ++g) acc -= r[LR_A + g] * x[k * len + nb[g]];
-            x[k * len + nb[0]] = acc * r[LR_INVA];
-        }
+        lat_vel_surface<T, PZ>(L, B, 4 / NC, col, (int)blockIdx.x * tg.bs + (int)threadIdx.x, b, x);
         return;
     }
     const LatTile tile = lat_tile(tg, L.nz - 2, (int)blockIdx.x - sb, L.order);
@@ -424,28 +540,13 @@ __global__ void __launch_bounds__(256) k_lat_bp(Lat<T> L, LatSurf B, int col, in
     T* __restrict__ p = x + 3 * len;
     const T* __restrict__ g = b + 3 * len;
     const int cm = NC == 2 ? 1 : 3;
-    if ((int)blockIdx.x < sb) {
-        int X, Y, Z;
-        if (!lat_surf_lane(L, B, 1, 0, (int)blockIdx.x * tg.bs + (int)threadIdx.x, &X, &Y, &Z)) return;
-        const T* __restrict__ r = L.rec + (size_t)L.rid[lat_rid_index(L, X, Y, Z)] * LR_SIZE;
-        int nb[15];
-        lat_taps(L, X, Y, Z, nb);
-        T s = -g[nb[0]];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int t = 0; t < 15; ++t) s += r[LR_B + 15 * k + t] * x[k * len + nb[t]];
-        if (((X + Y + Z) & cm) == col) {
-            T cp = T(0);
-#pragma unroll
-            for (int t = 0; t < 7; ++t) cp += r[LR_C + t] * p[nb[t]];
-            p[nb[0]] += omega * (s - cp) * r[LR_INVC];
-            if (!all) return;
-        }
-        sx[nb[0]] = s;
+    LatTile tile;
+    bool ok;
+    int X, Y, Z;
+    if (lat_surf_work(L, B, sb, tg, L.ny - 2, L.nz - 2, &tile, &ok, &X, &Y, &Z)) {
+        if (ok) lat_bp_surface<T>(L, X, Y, Z, cm, col, g, x, sx, omega, all);
         return;
     }
-    const LatTile tile = lat_tile(tg, L.nz - 2, (int)blockIdx.x - sb, L.order);
     if (!tile.ok) return;
     const LatPair P = lat_quad_lane(L, tg, tile, threadIdx.x);
     if (!P.ok) return;
@@ -559,39 +660,16 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
     const T* __restrict__ p = x + 3 * len;
     double acc = 0.0;
     int slot = -1;
-    if ((int)blockIdx.x < sb) {
-        if ((int)blockIdx.x * tg.bs < B.beg[6]) slot = tg.total + (int)blockIdx.x;
-        int X, Y, Z;
-        if (lat_surf_lane(L, B, 1, 0, (int)blockIdx.x * tg.bs + (int)threadIdx.x, &X, &Y, &Z)) {
-            const int id = L.rid[lat_rid_index(L, X, Y, Z)];
-            const T* __restrict__ rc = L.rec + (size_t)id * LR_SIZE;
-            int nb[15];
-            lat_taps(L, X, Y, Z, nb);
-            T v = AP ? T(0) : b[3 * len + nb[0]];
-#pragma unroll
-            for (int t = 0; t < 7; ++t) v += rc[LR_C + t] * p[nb[t]];
-#pragma unroll 1
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int t = 0; t < 15; ++t) v -= rc[LR_B + 15 * k + t] * x[k * len + nb[t]];
-            if (WR) r[3 * len + nb[0]] = AP ? -v : v;
-            if (NRM) acc += (double)v * (double)v;
-            const bool dir = L.rdir[id] != 0;
-#pragma unroll 1
-            for (int k = 0; k < 3; ++k) {
-                T w = T(0);
-                if (!dir) {
-                    w = AP ? T(0) : b[k * len + nb[0]];
-#pragma unroll
-                    for (int t = 0; t < 15; ++t) w -= rc[LR_BT + 15 * k + t] * p[nb[t]];
-                    for (int t = 0; t < 7; ++t) w -= rc[LR_A + t] * x[k * len + nb[t]];
-                }
-                if (WR) r[k * len + nb[0]] = AP ? -w : w;
-                if (NRM) acc += (double)w * (double)w;
-            }
-        }
+    LatTile tile;
+    bool ok;
+    int X, Y, Z;
+    if (lat_surf_work(L, B, sb, tg, L.ny - 2, L.nz - 2, &tile, &ok, &X, &Y, &Z)) {
+        if ((int)blockIdx.x >= sb)
+            slot = tile.t;
+        else if ((int)blockIdx.x * tg.bs < B.beg[6])
+            slot = tg.total + (int)blockIdx.x;
+        if (ok) acc = lat_res_surface<T, WR, NRM, AP>(L, X, Y, Z, b, x, r);
     } else {
-        const LatTile tile = lat_tile(tg, L.nz - 2, (int)blockIdx.x - sb, L.order);
         slot = tile.t;
         const LatPair P = lat_quad_lane(L, tg, tile, threadIdx.x);
         if (tile.ok && P.ok) {
@@ -668,6 +746,327 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
     }
 }
 
+// ---------------------------------------------------------------------------
+// Large levels in the red-black ordering with one viscosity (KIND 0): a lane takes
+// the quads of a block of 2 x 2 rows (y0, y0 + 1) x (z0, z0 + 1), y0 and z0 odd.
+// The one-row kernels above run at the rate of L2 requests (85 G lines/s, 11 TB/s,
+// of which HBM sees half): every tap row of a wave is fetched from L2 again, since
+// the L1 does not hold the rows of 16 waves.  A block of four rows reads 14 rows
+// where four single rows read 28 (the seven rows of B and B^T), and 12 where they
+// read 20 (the five rows of A and C).  Rows past the box (a side has an odd number
+// of interior rows) are clamped into it; what they give is not stored.  Parities
+// are constants: y0 + z0 is even.  17 M vertices, FP64 / FP32: the velocity sweep
+// 209 -> 195 / 127 -> 104 us (3.8 / 3.6 TB/s of the bytes it cannot do without),
+// B u with the red pressures 340 -> 274 / 222 -> 178 us; at 2.1 M vertices the 512
+// workgroups leave the chip half empty (19.2 -> 21.7 and 40.3 -> 42.0 us, FP64), hence
+// the rule of eight workgroups per CU.  The residual (k_lat_res) lost in this form:
+// its 64 sums leave two waves per SIMD (448 -> 590 us).
+// ---------------------------------------------------------------------------
+template <typename T>
+struct LatBlock {
+    int y0, z0, q;
+    unsigned v0, v2;   // byte offsets of rows y0 and y0 + 2 in a plane
+    bool ok;
+    // uniform base of row (dy, dz): the lane adds v0 (v2 for dy = 2)
+    template <int DY, int DZ, typename F>
+    __host__ __device__ __forceinline__ F* base(const Lat<T>& L, F* f, int sub) const {
+        const int z = DZ == 2 ? (z0 + 2 < L.nz ? z0 + 2 : L.nz - 1) : z0 + DZ;
+        return f + (ptrdiff_t)z * L.ZS + ((DY == 2 ? 0 : DY * L.RS) + sub);
+    }
+    template <int DY, int DZ, typename F>
+    __host__ __device__ __forceinline__ F* at(const Lat<T>& L, F* f, int sub) const {
+        using C = typename std::conditional<std::is_const<F>::value, const char, char>::type;
+        return (F*)((C*)base<DY, DZ>(L, f, sub) + (DY == 2 ? v2 : v0));
+    }
+    // what follows is not moved ahead of this point
+    __device__ __forceinline__ void anew() {
+        asm volatile("" : "+v"(v0), "+v"(v2));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // row (oy, oz) of the block is an interior row
+    __host__ __device__ bool in(const Lat<T>& L, int oy, int oz) const {
+        return y0 + oy <= L.ny - 2 && z0 + oz <= L.nz - 2;
+    }
+};
+template <typename T>
+__host__ __device__ __forceinline__ int lat_block_lanes(const Lat<T>& L) { return L.ny / 2 * L.Qi; }   // per plane pair
+template <typename T>
+__host__ __device__ __forceinline__ LatBlock<T> lat_block_lane(const Lat<T>& L, const LatGrid& tg,
+                                                               const LatTile& tile, int lane) {
+    LatBlock<T> P;
+    const int item = tile.part * tg.bs + lane, row = lat_div(item, tg.inv_row);
+    P.z0 = 2 * tile.z + 1;
+    P.y0 = 2 * row + 1;
+    P.q = item - row * L.Qi;
+    P.ok = row < L.ny / 2;
+    P.v0 = (unsigned)((P.y0 * L.RS + P.q) * (int)sizeof(T));
+    P.v2 = P.v0 + (unsigned)((P.y0 + 2 < L.ny ? 2 : 1) * L.RS * (int)sizeof(T));
+    return P;
+}
+// the offset of row (dy, dz) from output row (oy, oz): 0 itself, 1, 2 +-y, 3, 4
+// +-z, 5, 6 +-(y + z), -1 none
+__host__ __device__ constexpr int lat_rel(int dy, int dz, int oy, int oz) {
+    return dy == oy && dz == oz          ? 0
+           : dy == oy + 1 && dz == oz     ? 1
+           : dy == oy - 1 && dz == oz     ? 2
+           : dy == oy && dz == oz + 1     ? 3
+           : dy == oy && dz == oz - 1     ? 4
+           : dy == oy + 1 && dz == oz + 1 ? 5
+           : dy == oy - 1 && dz == oz - 1 ? 6
+                                          : -1;
+}
+// whether any output row of the block reads row (dy, dz): among its 7 or 5 rows
+__host__ __device__ constexpr bool lat_reads(int dy, int dz, int most) {
+    for (int o = 0; o < 4; ++o) {
+        const int r = lat_rel(dy, dz, o & 1, o >> 1);
+        if (r >= 0 && r <= most) return true;
+    }
+    return false;
+}
+// entries x = 4q - 1 .. 4q + 4 of row (DY, DZ) at e[0..5]
+template <int DY, int DZ, typename T>
+__device__ __forceinline__ void lat_row6(const Lat<T>& L, const LatBlock<T>& P, const T* f, T e[6]) {
+    const typename V2<T>::type l = ld2(P.template at<DY, DZ>(L, f, 0), 0);
+    const typename V2<T>::type r = ld2(P.template at<DY, DZ>(L, f, 3 * L.Qp - 1), 0);
+    e[0] = r[0];
+    e[1] = l[0];
+    e[2] = *P.template at<DY, DZ>(L, f, 2 * L.Qp);
+    e[3] = *P.template at<DY, DZ>(L, f, L.Qp);
+    e[4] = r[1];
+    e[5] = l[1];
+}
+// what a row at relation r adds to sum_pairs w[q] (u(+d) - u(-d)) at position j
+template <int R, typename T, typename W>
+__device__ __forceinline__ T lat_row_diff(const W& w, const T e[6], int j) {
+    if (R == 0) return w[0] * (e[j + 2] - e[j]);
+    if (R == 1) return w[1] * e[j + 1] + w[3] * e[j + 2];
+    if (R == 2) return -(w[1] * e[j + 1] + w[3] * e[j]);
+    if (R == 3) return w[2] * e[j + 1] + w[5] * e[j + 2];
+    if (R == 4) return -(w[2] * e[j + 1] + w[5] * e[j]);
+    if (R == 5) return w[4] * e[j + 1] + w[6] * e[j + 2];
+    return -(w[4] * e[j + 1] + w[6] * e[j]);
+}
+// rows of the block's neighbourhood, body(dy, dz) as constants.  Two rows are in
+// flight per wave: with all of them the loads' registers leave two waves per SIMD
+// (k_lat_bp_blk at 8 refinements 406 us, with two rows 287 us)
+template <int MOST, typename P, typename F>
+__device__ __forceinline__ void lat_rows(P& blk, F&& body) {
+    auto one = [&](auto dyc, auto dzc) __attribute__((always_inline)) {
+        if constexpr (lat_reads(decltype(dyc)::value, decltype(dzc)::value, MOST)) body(dyc, dzc);
+    };
+    using std::integral_constant;
+#define LAT_ROWS(y, z) \
+    one(integral_constant<int, y>{}, integral_constant<int, z>{}); \
+    one(integral_constant<int, y + 1>{}, integral_constant<int, z>{}); \
+    blk.anew()
+    LAT_ROWS(-1, -1);
+    LAT_ROWS(1, -1);
+    LAT_ROWS(-1, 0);
+    LAT_ROWS(1, 0);
+    LAT_ROWS(-1, 1);
+    LAT_ROWS(1, 1);
+    LAT_ROWS(-1, 2);
+    LAT_ROWS(1, 2);
+#undef LAT_ROWS
+}
+// the value is worked out here, not where it is (conditionally) stored
+template <typename T>
+__device__ __forceinline__ void lat_pin(T& v) {
+    asm volatile("" : "+v"(v));
+}
+// body(o) for the four output rows, o a constant
+template <typename F>
+__device__ __forceinline__ void lat_four(F&& body) {
+    body(std::integral_constant<int, 0>{});
+    body(std::integral_constant<int, 1>{});
+    body(std::integral_constant<int, 2>{});
+    body(std::integral_constant<int, 3>{});
+}
+// body(output row o, relation) for the output rows that read row (dy, dz)
+template <int MOST, int DY, int DZ, typename F>
+__device__ __forceinline__ void lat_outs(F&& body) {
+    using std::integral_constant;
+    auto one = [&](auto oc) __attribute__((always_inline)) {
+        constexpr int o = decltype(oc)::value, r = lat_rel(DY, DZ, o & 1, o >> 1);
+        if constexpr (r >= 0 && r <= MOST) body(oc, integral_constant<int, r>{});
+    };
+    one(integral_constant<int, 0>{});
+    one(integral_constant<int, 1>{});
+    one(integral_constant<int, 2>{});
+    one(integral_constant<int, 3>{});
+}
+// first position of parity col in output row o of a block (y0 + z0 even)
+__host__ __device__ constexpr int lat_first(int col, int o) { return (col + (o & 1) + (o >> 1)) & 1; }
+
+template <typename T, int COL, bool PZ>
+__global__ void __launch_bounds__(256, 4) k_lat_vel_blk(Lat<T> L, LatSurf B, int sb, LatGrid tg,
+                                                     const T* __restrict__ b, T* __restrict__ x) {
+    const size_t len = L.len;
+    const T* __restrict__ p = x + 3 * len;
+    if ((int)blockIdx.x < sb) {
+        lat_vel_surface<T, PZ>(L, B, 2, COL, (int)blockIdx.x * tg.bs + (int)threadIdx.x, b, x);
+        return;
+    }
+    LatTile tile = lat_tile(tg, L.nz / 2, (int)blockIdx.x - sb, L.order);
+    tile.z = __builtin_amdgcn_readfirstlane(tile.z);
+    if (!tile.ok) return;
+    LatBlock<T> P = lat_block_lane(L, tg, tile, threadIdx.x);
+    if (!P.ok) return;
+    const int Qp = L.Qp;
+    T t[4][3][2];
+    lat_four([&](auto oc) __attribute__((always_inline)) {
+        constexpr int o = decltype(oc)::value;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                t[o][k][e] = *P.template at<(o & 1), (o >> 1)>(L, b + k * len, lat_sub(lat_first(COL, o) + 2 * e, Qp));
+    });
+    if (!PZ)
+        lat_rows<6>(P, [&](auto dyc, auto dzc) __attribute__((always_inline)) {
+            constexpr int dy = decltype(dyc)::value, dz = decltype(dzc)::value;
+            T e[6];
+            lat_row6<dy, dz>(L, P, (const T*)p, e);
+            lat_outs<6, dy, dz>([&](auto oc, auto rc) __attribute__((always_inline)) {
+                constexpr int o = decltype(oc)::value, s0 = lat_first(COL, o);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        t[o][k][h] -= lat_row_diff<decltype(rc)::value>(L.bt[k], e, s0 + 2 * h);
+                        lat_pin(t[o][k][h]);
+                    }
+            });
+        });
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const T* __restrict__ u = x + k * len;
+        lat_rows<4>(P, [&](auto dyc, auto dzc) __attribute__((always_inline)) {
+            constexpr int dy = decltype(dyc)::value, dz = decltype(dzc)::value;
+            // the row's vertices of the other parity, positions b0, b0 + 2 (and
+            // one more beside the quad for the row's own update)
+            constexpr int b0 = (1 + COL + dy + dz + 4) & 1;
+            constexpr bool own = lat_rel(dy, dz, dy, dz) == 0 && dy >= 0 && dy < 2 && dz >= 0 && dz < 2;
+            T e[6];
+            e[b0 + 1] = *P.template at<dy, dz>(L, u, lat_sub(b0, Qp));
+            e[b0 + 3] = *P.template at<dy, dz>(L, u, lat_sub(b0 + 2, Qp));
+            if (own) {
+                if (b0 == 1)
+                    e[0] = *P.template at<dy, dz>(L, u, 3 * Qp - 1);
+                else
+                    e[5] = *P.template at<dy, dz>(L, u, 1);
+            }
+            lat_outs<4, dy, dz>([&](auto oc, auto rc) __attribute__((always_inline)) {
+                constexpr int o = decltype(oc)::value, r = decltype(rc)::value, s0 = lat_first(COL, o);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int j = s0 + 2 * h + 1;
+                    t[o][k][h] -= r == 0 ? L.a[0] * (e[j + 1] + e[j - 1]) : (r <= 2 ? L.a[1] : L.a[2]) * e[j];
+                }
+            });
+        });
+        lat_four([&](auto oc) __attribute__((always_inline)) {
+            constexpr int o = decltype(oc)::value;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) lat_pin(t[o][k][h]);
+            if (!P.in(L, o & 1, o >> 1)) return;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int j = lat_first(COL, o) + 2 * h;
+                if (j == 0 && P.q == 0) continue;   // x = 0
+                *P.template at<(o & 1), (o >> 1)>(L, x + k * len, lat_sub(j, Qp)) = t[o][k][h] * L.inva;
+            }
+        });
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256, 4) k_lat_bp_blk(Lat<T> L, LatSurf B, int sb, LatGrid tg,
+                                                    const T* __restrict__ b, T* __restrict__ x,
+                                                    T* __restrict__ sx, T omega, int all) {
+    const size_t len = L.len;
+    T* __restrict__ p = x + 3 * len;
+    const T* __restrict__ g = b + 3 * len;
+    LatTile tile;
+    bool ok;
+    int X, Y, Z;
+    if (lat_surf_work(L, B, sb, tg, L.ny / 2, L.nz / 2, &tile, &ok, &X, &Y, &Z)) {
+        if (ok) lat_bp_surface<T>(L, X, Y, Z, 1, 0, g, x, sx, omega, all);
+        return;
+    }
+    tile.z = __builtin_amdgcn_readfirstlane(tile.z);
+    if (!tile.ok) return;
+    LatBlock<T> P = lat_block_lane(L, tg, tile, threadIdx.x);
+    if (!P.ok) return;
+    const int Qp = L.Qp;
+    T s[4][4], cp[4][2], p0[4][2];
+    lat_four([&](auto oc) __attribute__((always_inline)) {
+        constexpr int o = decltype(oc)::value;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[o][j] = -*P.template at<(o & 1), (o >> 1)>(L, g, lat_sub(j, Qp));
+    });
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        const T* __restrict__ u = x + k * len;
+        lat_rows<6>(P, [&](auto dyc, auto dzc) __attribute__((always_inline)) {
+            constexpr int dy = decltype(dyc)::value, dz = decltype(dzc)::value;
+            T e[6];
+            lat_row6<dy, dz>(L, P, (const T*)u, e);
+            lat_outs<6, dy, dz>([&](auto oc, auto rc) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    s[decltype(oc)::value][j] -= lat_row_diff<decltype(rc)::value>(L.bt[k], e, j);
+            });
+        });
+    }
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) cp[o][h] = T(0);
+    lat_rows<4>(P, [&](auto dyc, auto dzc) __attribute__((always_inline)) {
+        constexpr int dy = decltype(dyc)::value, dz = decltype(dzc)::value;
+        constexpr bool own = dy >= 0 && dy < 2 && dz >= 0 && dz < 2;
+        constexpr int b0 = (1 + dy + dz + 4) & 1;   // black positions of the row
+        T e[6];
+        if (own) {
+            lat_row6<dy, dz>(L, P, (const T*)p, e);
+        } else {
+            e[b0 + 1] = *P.template at<dy, dz>(L, p, lat_sub(b0, Qp));
+            e[b0 + 3] = *P.template at<dy, dz>(L, p, lat_sub(b0 + 2, Qp));
+        }
+        lat_outs<4, dy, dz>([&](auto oc, auto rc) __attribute__((always_inline)) {
+            constexpr int o = decltype(oc)::value, r = decltype(rc)::value, s0 = lat_first(0, o);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int j = s0 + 2 * h + 1;
+                if (r == 0) {
+                    p0[o][h] = e[j];
+                    cp[o][h] += L.c0 * e[j] + L.c[0] * (e[j + 1] + e[j - 1]);
+                } else {
+                    cp[o][h] += (r <= 2 ? L.c[1] : L.c[2]) * e[j];
+                }
+            }
+        });
+    });
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) lat_pin(cp[o][h]);
+    lat_four([&](auto oc) __attribute__((always_inline)) {
+        constexpr int o = decltype(oc)::value;
+        if (!P.in(L, o & 1, o >> 1)) return;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j == 0 && P.q == 0) continue;   // x = 0
+            const bool red = ((j + lat_first(0, o)) & 1) == 0;
+            if (red)
+                *P.template at<(o & 1), (o >> 1)>(L, p, lat_sub(j, Qp)) =
+                    p0[o][j / 2] + omega * (s[o][j] - cp[o][j / 2]) * L.invc;
+            if (!red || all) *P.template at<(o & 1), (o >> 1)>(L, sx, lat_sub(j, Qp)) = s[o][j];
+        }
+    });
+}
+
 // t_k = b_k - (A u)_k (k = 0..2; Dirichlet rows 0): the velocity residual of the
 // velocity multigrid.
 template <typename T, int KIND>
@@ -675,9 +1074,11 @@ __global__ void __launch_bounds__(256) k_lat_ares(Lat<T> L, LatSurf B, int sb, L
                                                   const T* __restrict__ b, const T* __restrict__ x,
                                                   T* __restrict__ r) {
     const size_t len = L.len;
-    if ((int)blockIdx.x < sb) {
-        int X, Y, Z;
-        if (!lat_surf_lane(L, B, 1, 0, (int)blockIdx.x * tg.bs + (int)threadIdx.x, &X, &Y, &Z)) return;
+    LatTile tile;
+    bool ok;
+    int X, Y, Z;
+    if (lat_surf_work(L, B, sb, tg, L.ny - 2, L.nz - 2, &tile, &ok, &X, &Y, &Z)) {
+        if (!ok) return;
         const int id = L.rid[lat_rid_index(L, X, Y, Z)];
         const T* __restrict__ rc = L.rec + (size_t)id * LR_SIZE;
         const bool dir = L.rdir[id] != 0;
@@ -694,7 +1095,6 @@ __global__ void __launch_bounds__(256) k_lat_ares(Lat<T> L, LatSurf B, int sb, L
         }
         return;
     }
-    const LatTile tile = lat_tile(tg, L.nz - 2, (int)blockIdx.x - sb, L.order);
     if (!tile.ok) return;
     const LatPair P = lat_quad_lane(L, tg, tile, threadIdx.x);
     if (!P.ok) return;
@@ -738,9 +1138,11 @@ __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSur
                                                       const T* __restrict__ rf, T* __restrict__ bc,
                                                       T* __restrict__ xc) {
     const size_t lc = C.len, lf = F.len;
-    if ((int)blockIdx.x < sb) {
-        int X, Y, Z;
-        if (!lat_surf_lane(C, B, 1, 0, (int)blockIdx.x * tg.bs + (int)threadIdx.x, &X, &Y, &Z)) return;
+    LatTile tile;
+    bool ok;
+    int X, Y, Z;
+    if (lat_surf_work(C, B, sb, tg, C.ny - 2, C.nz - 2, &tile, &ok, &X, &Y, &Z)) {
+        if (!ok) return;
         const bool dir = C.rdir[C.rid[lat_rid_index(C, X, Y, Z)]] != 0;
         const int a = lat_at(C, X, Y, Z);
         int nb[15];
@@ -757,7 +1159,6 @@ __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSur
         }
         return;
     }
-    const LatTile tile = lat_tile(tg, C.nz - 2, (int)blockIdx.x - sb, C.order);
     if (!tile.ok) return;
     const LatPair P = lat_quad_lane(C, tg, tile, threadIdx.x);
     if (!P.ok) return;

@@ -77,6 +77,9 @@ CASES = [
     ((1, 1, 1), 6, 1.0, False, {"ordering": 2, "p_sweep": 1}),
     ((1, 1, 1), 7, 1.0, False, {"ordering": 2, "nu1": 1, "nu2": 1}),
     ((3, 1, 1), 6, 6.0, True, {"nu1": 1, "nu2": 1}),
+    # the smallest levels with blocks of 2 x 2 rows
+    ((4, 1, 1), 7, 1.0, True, {"ordering": 2, "p_sweep": 1, "nu1": 2, "nu2": 1}),
+    ((1, 4, 1), 7, 1.0, False, {"ordering": 2, "block_order": 2, "nu1": 1, "nu2": 2}),
 ]
 
 
