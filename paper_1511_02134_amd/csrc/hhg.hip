@@ -25,7 +25,10 @@ using namespace hhg;
 // runs on holds its own copy until the process ends.  In host code the
 // array's name is not a device address: the address of the current device's
 // copy comes from hipGetSymbolAddress (scratch_address below).
-constexpr size_t NOALLOC_SCRATCH_DOUBLES = size_t(1) << 20;   // 8 MiB
+// Levels of up to 2^20 sums are taken, counted as one per tile below SPLIT_MIN_N
+// intervals; launches of one vertex per lane write four per tile there.
+constexpr size_t NOALLOC_MAX_PARTIALS = size_t(1) << 20;
+constexpr size_t NOALLOC_SCRATCH_DOUBLES = 4 * NOALLOC_MAX_PARTIALS;   // 32 MiB
 static __device__ __align__(256) double scratch[NOALLOC_SCRATCH_DOUBLES];
 
 namespace {
@@ -1213,16 +1216,20 @@ inline int full_vblocks(int mode, int n_vtiles) {
 // and the interface blocks of K x and the residual separately: the volume
 // kernel is then not held to the interface lanes' register budget
 constexpr int SPLIT_MIN_N = 64;
+// general meshes (one vertex per lane below SPLIT_MIN_N too).  A shell of 480
+// macros, the residual with one launch / with two: n = 8 27 / 38 us, n = 16
+// 69 / 61 us, n = 32 168 / 136 us
+constexpr int SPLIT_MIN_N_GEN = 16;
 
 // K x or the residual (MODE_APPLY / MODE_RES); MIRROR: interface taps from
 // the level's mirror of x
-template <typename T, int MODE, bool MIRROR, bool DOP>
+template <typename T, int MODE, bool MIRROR, bool DOP, bool GEN>
 void launch_kx_op(LevelDev<T>& v, int ib, const T* x, const T* b, T* y, double* partials,
                   hipStream_t s) {
-    if (v.n >= SPLIT_MIN_N) {
-        if constexpr (DOP) {
+    if (v.n >= (GEN ? SPLIT_MIN_N_GEN : SPLIT_MIN_N)) {
+        if constexpr (DOP || GEN) {
             // volume launch: one vertex per lane (four blocks per tile)
-            hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 1, DOP>),
+            hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 1, DOP, GEN>),
                                dim3(full_blocks(v.n_vtiles)), dim3(TPB), 0, s, v, x, b, y, partials,
                                0, (T*)nullptr, -1, T(0));
         } else {
@@ -1231,31 +1238,36 @@ void launch_kx_op(LevelDev<T>& v, int ib, const T* x, const T* b, T* y, double* 
                                dim3(TPB), 0, s, v, x, b, y, partials, 0, (T*)nullptr, -1, T(0));
         }
         if (ib > 0)
-            hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 2, DOP>), dim3(ib), dim3(TPB), 0,
-                               s, v, x, b, y, partials, ib, (T*)nullptr, -1, T(0));
+            hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 2, DOP, GEN>), dim3(ib), dim3(TPB),
+                               0, s, v, x, b, y, partials, ib, (T*)nullptr, -1, T(0));
         return;
     }
-    hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 0, DOP>), dim3(ib + v.n_vtiles),
-                       dim3(TPB), 0, s, v, x, b, y, partials, ib, (T*)nullptr, -1, T(0));
+    hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 0, DOP, GEN>),
+                       dim3(ib + (GEN ? full_blocks(v.n_vtiles) : v.n_vtiles)), dim3(TPB), 0, s, v, x, b, y,
+                       partials, ib, (T*)nullptr, -1, T(0));
 }
 
-// the velocity form of the context: Laplace (a_1) or D (a_2); the residual's
-// per-block partial sums go to `partials` (the workspace's by default)
+// the velocity form of the context: D (a_2), Laplace (a_1) on general meshes
+// (15-tap rows of each component: as point blocks of which two thirds are zeros
+// the residual on a shell of 480 macros took 44 / 106 / 213 us at 3 / 4 / 5
+// refinements, now 27 / 61 / 136 us) or on Kuhn meshes; the residual's per-block partial sums go to `partials` (the workspace's by default)
 template <typename T, int MODE, bool MIRROR>
 void launch_kx(hhg_ctx* c, LevelDev<T>& v, int ib, const T* x, const T* b, T* y, hipStream_t s,
                double* partials = nullptr) {
     if (!partials) partials = c->partials;
-    if (dpath(c))
-        launch_kx_op<T, MODE, MIRROR, true>(v, ib, x, b, y, partials, s);
+    if (c->opts.op == 1)
+        launch_kx_op<T, MODE, MIRROR, true, false>(v, ib, x, b, y, partials, s);
+    else if (c->mi.general)
+        launch_kx_op<T, MODE, MIRROR, false, true>(v, ib, x, b, y, partials, s);
     else
-        launch_kx_op<T, MODE, MIRROR, false>(v, ib, x, b, y, partials, s);
+        launch_kx_op<T, MODE, MIRROR, false, false>(v, ib, x, b, y, partials, s);
 }
 
 // number of per-block partial sums of a residual on level l (the entries
 // k_reduce_sum adds up): the volume ones, then one per interface block
 template <typename T>
-inline int residual_partials(const LevelDev<T>& v) {
-    return (v.n >= SPLIT_MIN_N ? 4 : 1) * v.nv_nat + (v.nif + TPB - 1) / TPB;
+inline int residual_partials(const hhg_ctx* c, const LevelDev<T>& v) {
+    return (v.n >= SPLIT_MIN_N || (c->mi.general && c->opts.op == 0) ? 4 : 1) * v.nv_nat + (v.nif + TPB - 1) / TPB;
 }
 
 // levels with at least this many intervals per macro edge evaluate RU and BP
@@ -1299,9 +1311,7 @@ template <typename T>
 void residual_mirror(hhg_ctx* c, int l, const T* x, const T* b, T* r, hipStream_t s) {
     LevelDev<T>& v = view<T>(c, l);
     const int ib = iface_blocks(v.nif);
-    const int grid = ib + full_vblocks(MODE_RES, v.n_vtiles);
     Timed tm(c, HHG_K_APPLY, s, l == c->L, c->bytes_res);
-    (void)grid;
     ops(c, l, 1, 2, 1, 0);
     launch_kx<T, MODE_RES, true>(c, v, ib, x, b, r, s);
 }
@@ -1332,7 +1342,7 @@ void residual_norm_t(hhg_ctx* c, int l, const T* x, const T* b, T* t, double* ou
         }
     }
     hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(RTPB), 0, s, c->partials,
-                       residual_partials(v), out, 1);
+                       residual_partials(c, v), out, 1);
 }
 
 // mirror of x taken afresh (entry points that smooth a caller's vector)
@@ -1626,14 +1636,12 @@ void residual_norm(hhg_ctx* c, int l, const T* x, const T* b, T* r, double* out,
     if (mirror) {
         residual_mirror<T>(c, l, x, b, r, s);
     } else {
-        const int grid = ib + full_vblocks(MODE_RES, v.n_vtiles);
         Timed tm(c, HHG_K_APPLY, s, l == c->L, c->bytes_res);
-        (void)grid;
         ops(c, l, 1, 2, 1, 0);
         launch_kx<T, MODE_RES, false>(c, v, ib, x, b, r, s);
     }
     hipLaunchKernelGGL(k_reduce_sum, dim3(1), dim3(RTPB), 0, s, c->partials,
-                       residual_partials(v), out, 1);
+                       residual_partials(c, v), out, 1);
 }
 
 template <typename T, int NF = 4>
@@ -2570,11 +2578,11 @@ hhg_status hhg_residual_noalloc(hhg_ctx* c, int32_t l, const void* x, const void
     if (hipGetDevice(&dev) != hipSuccess || dev != c->dev)
         return fail(c, HHG_EINVAL, "the context's device must be the current device");
     LevelDev<double>& v = view<double>(c, l);
-    const int np = residual_partials(v);
-    if ((size_t)np > NOALLOC_SCRATCH_DOUBLES)
+    const int np = residual_partials(c, v), most = (v.n >= SPLIT_MIN_N ? 4 : 1) * v.nv_nat + (v.nif + TPB - 1) / TPB;
+    if ((size_t)most > NOALLOC_MAX_PARTIALS)
         return fail(c, HHG_EINVAL,
-                    "level too large for the static scratch: " + std::to_string(np) +
-                        " partial sums, at most " + std::to_string(NOALLOC_SCRATCH_DOUBLES));
+                    "level too large for the static scratch: " + std::to_string(most) +
+                        " partial sums, at most " + std::to_string(NOALLOC_MAX_PARTIALS));
     hipStream_t s = (hipStream_t)stream;
     // every partial in [0, np) is written by its block before the sum reads
     // it, so the scratch needs no clearing between calls

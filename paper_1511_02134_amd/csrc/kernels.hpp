@@ -946,9 +946,12 @@ __host__ __device__ __forceinline__ int full_blocks(int n_vtiles) { return 4 * (
 // The passes that read all four fields at every tap (K x, the residual, the
 // right-hand side and the forcing gradient) keep one block per tile and four
 // vertices per lane, evaluated one after another: one vertex per lane would
-// need every tap of all fields in flight at once (over 256 VGPRs).
-__host__ __device__ constexpr bool quad_lanes(int mode) {
-    return mode == MODE_APPLY || mode == MODE_RES || mode == MODE_RHS || mode == MODE_GRADF;
+// need every tap of all fields in flight at once (over 256 VGPRs).  K x and the
+// residual on general meshes (gen: 15-tap rows of every block) do take one vertex
+// per lane: 136 VGPRs in a launch of their own, and no pair symmetries to gain
+// from (n = 32, 480 macros: 213 -> 136 us).
+__host__ __device__ constexpr bool quad_lanes(int mode, bool gen = false) {
+    return ((mode == MODE_APPLY || mode == MODE_RES) && !gen) || mode == MODE_RHS || mode == MODE_GRADF;
 }
 
 // Quad windows: a lane that evaluates the 4 vertices i = 4q..4q+3 of a row
@@ -1235,8 +1238,8 @@ __device__ __forceinline__ void quad_fused_axis(const LevelDev<T>& L, const T* _
 // PART 1 / 2: a launch of the volume blocks only (ib = 0) or of the interface
 // blocks only (grid = ib); each then gets the registers of its own branch.
 // DOP (K x and the residual only): the D form a_2, every row from eval_node.
-// GEN (fused passes only): the fused colour update of a general mesh, whose
-// a_1 and c_l couple all 14 neighbours.
+// GEN: a_1 and c_l of a general mesh couple all 14 neighbours (the fused colour
+// update; the rows of K x and the residual, from eval_node).
 // TOUT (residual, Laplace form): the residual only enters the partial sums of
 // its norm; y receives t = b_k - (B^T p)_k (k = 0..2) instead, the values of
 // the f - B^T p pass up to rounding, for a smoothing step that follows at once.
@@ -1330,7 +1333,7 @@ __global__ void __launch_bounds__(TPB) k_full(LevelDev<T> L, const T* __restrict
                 }
             }
         }
-    } else if (quad_lanes(MODE) && PART == 0 && vol) {
+    } else if (quad_lanes(MODE, GEN) && PART == 0 && vol) {
         const Tile tl = L.vtiles[blockIdx.x - ib];
         slot = tl.nat;
         if (tl.macro >= 0) {
@@ -1392,7 +1395,7 @@ __global__ void __launch_bounds__(TPB) k_full(LevelDev<T> L, const T* __restrict
                         eval_ares<T>(st, tp, ca, false, x, len, b, len, s[0], out);
                     } else if (DOP) {
                         eval_node<T, MODE, true>(st, s, false, x, len, b, len, s[0], out);
-                    } else if (MODE == MODE_APPLY || MODE == MODE_RES) {
+                    } else if ((MODE == MODE_APPLY || MODE == MODE_RES) && !GEN) {
                         eval_vol_pairs<T, MODE>(st, s, x, b, len, out);
                     } else {
                         eval_node<T, MODE>(st, s, false, x, len, b, len, s[0], out);
@@ -1467,7 +1470,7 @@ __global__ void __launch_bounds__(TPB) k_full(LevelDev<T> L, const T* __restrict
         }
     } else {
         if ((int)blockIdx.x * TPB < L.nif)
-            slot = (quad_lanes(MODE) && PART == 0 ? 1 : 4) * L.nv_nat + (int)blockIdx.x;
+            slot = (quad_lanes(MODE, GEN) && PART == 0 ? 1 : 4) * L.nv_nat + (int)blockIdx.x;
         const int t = (int)blockIdx.x * TPB + (int)threadIdx.x;
         if (t < L.nif) {
             const T* st = L.st + (size_t)L.if_sid[t] * ST_SIZE;
