@@ -15,12 +15,14 @@ Printed as one JSON line with, besides the contract fields:
                   solve (hipEvent pairs around every phase), levels_ms the
                   same by level;
   roofline        the dominant kernel of the finest level, the velocity sweep
-                  or the fused f - B^T p pass, whichever has the larger total
-                  time in the timed solves (the other as roofline_<name>),
-                  against the 8 TB/s HBM peak: algorithmic bytes per launch /
-                  its mean launch time (hipEvents on its stream; one pair
-                  around the back-to-back velocity sweeps of each smoothing
-                  step, one around every fused pass);
+                  or the launch that forms f - B^T p (the first sweep of a step
+                  in the lattice cycles, where every sweep forms it; the fused
+                  pass elsewhere), whichever has the larger total time in the
+                  timed solves (the other as roofline_<name>), against the
+                  8 TB/s HBM peak: algorithmic bytes per launch / its mean
+                  launch time (hipEvents on its stream; one pair around the
+                  back-to-back velocity sweeps of each smoothing step, one
+                  around every other launch);
   mixed_precision the FP32-in-FP64 solve of the same problem;
   cpu_baseline    the FP64 oracle (numpy/scipy) solving the same problem at a
                   bounded size on the host, setup excluded.
@@ -50,6 +52,7 @@ TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_velocity_sweep_unitcub
 SHELL_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_velocity_sweep_shell_R7_fp64.md")
 RB_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles",
                                   "traffic_velocity_sweep_redblack_unitcube_R8_fp64.md")
+# the fused pass of hhg_smooth; the solver's cycles form f - B^T p in their sweeps
 RU_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_fused_ru_redblack_unitcube_R8_fp64.md")
 
 
@@ -534,6 +537,11 @@ def main():
     if nvel == 0:
         raise RuntimeError("no finest-level velocity sweep was timed")
     vs = 8.0 if precision == 0 else 4.0
+    # the cycles of the Laplace form in the colour and red-black orders run on
+    # the structured lattice; blocks of 2 x 2 rows from 8 M vertices on
+    lattice = not dform and ordering in (0, 2)
+    lat_vel = ("k_lat_vel_blk" if ordering == 2 and nvert >= 8.4e6 and float(nu.max()) == float(nu.min())
+               else "k_lat_vel")
     # algorithmic bytes of one colour launch: one direction of the velocity
     # Gauss-Seidel reads u (3 values), f (3) and p and writes u (3) per finest
     # vertex, 10 values; its four colour launches share them (the red-black
@@ -567,7 +575,7 @@ def main():
     prec_name = "double" if precision == 0 else "float"
     entries = {"velocity_sweep": {
         "bound": "hbm",
-        "kernel": (f"{'k_colour_rb' if ordering == 2 else 'k_colour'}<{prec_name},velocity"
+        "kernel": (f"{lat_vel if lattice else 'k_colour'}<{prec_name},velocity"
                    f"{',D' if dform else ''}> (finest level)"),
         "achieved": achieved,
         "peak": HBM_PEAK_GBS,
@@ -585,18 +593,17 @@ def main():
                        "frac_of_copy": achieved / copy_gbs},
     }}
     if nru > 0:
-        # f - B^T p with the fused update: read f (3 values), p, the other
-        # colours' velocity and write t (3) and the updated colour's velocity,
-        # per finest vertex: 10 values with a red-black parity, 9.25 with colour 0
-        ru_bytes = (10.0 if ordering == 2 else 9.25) * vs * nvert
+        # lattice cycles: a velocity sweep as above.  Elsewhere f - B^T p with
+        # the fused update: read f (3 values), p, the other colours' velocity
+        # and write t (3) and colour 0's velocity, 9.25 values per finest vertex
+        ru_bytes = alg_bytes if lattice else 9.25 * vs * nvert
         ru_avg_ms = ms_ru / nru
         ru_achieved = ru_bytes / (ru_avg_ms * 1e-3) / 1e9
-        ru_traffic = (measured_traffic(RU_TRAFFIC_PROFILE)
-                      if args.workload == 3 and not args.R and precision == 0 and not dform
-                      and ordering == 2 else None)
+        ru_traffic = traffic if lattice else None
         entries["fused_ru"] = {
             "bound": "hbm",
-            "kernel": f"k_full<{prec_name},f - B^T p,fused,windows> (finest level)",
+            "kernel": (f"{lat_vel}<{prec_name},velocity> (finest level, first sweep of a step)" if lattice
+                       else f"k_full<{prec_name},f - B^T p,fused,windows> (finest level)"),
             "achieved": ru_achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -604,10 +611,10 @@ def main():
             "traffic": ru_traffic,
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, "
                             "copy-calibrated)",
-            "bytes_model": ("read f (3 values), p and the other colours' velocity, write t (3) "
-                            "and the updated colour's velocity, per finest vertex: "
-                            + ("10 values (red parity)" if ordering == 2 else
-                               "9.25 values (colour 0)")),
+            "bytes_model": (entries["velocity_sweep"]["bytes_model"] if lattice else
+                            "read f (3 values), p and the other colours' velocity, write t (3) "
+                            "and the updated colour's velocity, per finest vertex: 9.25 values "
+                            "(colour 0)"),
             "bytes_per_launch": ru_bytes,
             "launches": nru,
             "avg_us": 1000.0 * ru_avg_ms,

@@ -136,7 +136,10 @@ typedef struct {
     int32_t graphs;       /* 1: hhg_solve captures the launches of one cycle and its
                              stopping test in a HIP graph on first use for an (x, b) pair
                              and replays it (at most four pairs kept; the capture records
-                             launches without running them); 0 (default): plain launches
+                             launches without running them; Kuhn meshes without free-slip
+                             faces, Laplace form, orderings 0 and 2: the cycles work on
+                             vectors of the context, and one graph serves every pair);
+                             0 (default): plain launches
                              on the stream.  Results are bitwise identical either way */
     int32_t op;           /* velocity form (Section 2.1, eq. varform): 0 the Laplace form
                              a_1 = <nu grad u, grad v> (default); 1 the D form
@@ -292,8 +295,8 @@ hhg_status hhg_residual(hhg_ctx* ctx, int32_t level, const void* d_x, const void
  * all pressure rows) written to the device scalar *d_norm instead of host
  * memory.  It allocates nothing, records no event and never synchronises:
  * its per-block partial sums live in a static device array of the library
- * (8 MiB, 2^20 doubles, one per GPU, held until the process ends); levels
- * needing more partial sums than that (beyond about 9 refinements of the
+ * (32 MiB, one per GPU, held until the process ends); levels needing
+ * more than 2^20 partial sums (beyond about 9 refinements of the
  * unit cube) return HHG_EINVAL.  Every call on one GPU shares that array, so
  * calls that overlap in time on one GPU (on different streams or host
  * threads) race; calls ordered on one stream do not.  The context's device
@@ -433,7 +436,10 @@ enum {
     HHG_K_APPLY = 2,   /* B^T p / B u / residual passes, finest level (the
                           fused f - B^T p pass excepted) */
     HHG_K_RU = 3,      /* f - B^T p with its fused colour-0 or red velocity
-                          update, finest level */
+                          update, finest level; in the cycles of Kuhn meshes
+                          without free-slip faces (Laplace form, orderings 0
+                          and 2), whose sweeps all form f - B^T p: the first
+                          sweep of a step that forms it */
     HHG_K_NCLASS = 4
 };
 hhg_status hhg_set_timing(hhg_ctx* ctx, int32_t on);

@@ -1250,7 +1250,8 @@ void launch_kx_op(LevelDev<T>& v, int ib, const T* x, const T* b, T* y, double* 
 // the velocity form of the context: D (a_2), Laplace (a_1) on general meshes
 // (15-tap rows of each component: as point blocks of which two thirds are zeros
 // the residual on a shell of 480 macros took 44 / 106 / 213 us at 3 / 4 / 5
-// refinements, now 27 / 61 / 136 us) or on Kuhn meshes; the residual's per-block partial sums go to `partials` (the workspace's by default)
+// refinements, now 27 / 61 / 136 us) or on Kuhn meshes; the residual's per-block
+// partial sums go to `partials` (the workspace's by default)
 template <typename T, int MODE, bool MIRROR>
 void launch_kx(hhg_ctx* c, LevelDev<T>& v, int ib, const T* x, const T* b, T* y, hipStream_t s,
                double* partials = nullptr) {

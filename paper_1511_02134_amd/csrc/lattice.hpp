@@ -18,6 +18,14 @@
 // are constants too; otherwise (KIND 1) a vertex's axis coefficients of A and
 // C come from a record that its cell and the order of its fractional
 // coordinates name.  Surface vertices read whole records.
+//
+// Measured against the per-macro kernels on 17 M vertices, FP64, red-black: an
+// Uzawa step took 527 (f - B^T p with the red update) + 2 x 240 + 433 + 86 us and
+// takes 3 x 195 + 274 + 61 us; the residual 679 and 655 us, restriction 258 and
+// 170, prolongation 431 and 248.  A solve pays the conversions at its ends, 0.71 ms
+// each.  Below 2 M vertices a launch takes 3 to 10 us whatever it computes: there
+// the gain is in launches (no f - B^T p pass, the visits) and in shorter chains of
+// dependent loads (no tile, neighbour and copy tables).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -120,13 +128,13 @@ struct LatGrid {
 // the lines of the volume rows (a vertex needs one or two entries of each), so
 // they go ahead of the rows of their group, in blocks of their own, and share
 // the lines in L2: as part of the surface lanes the two faces fetched them again.
-__host__ __device__ __forceinline__ LatGrid lat_grid(int lanes, int rows, int planes, int bs, int side = 0, int G = 8) {
+__host__ __device__ __forceinline__ LatGrid lat_grid(int lanes, int rows, int planes, int bs, int side = 0) {
     LatGrid g;
     const int per = (lanes + bs - 1) / bs;
     g.inv_row = (float)rows / (float)lanes;
     g.bs = bs;
     g.per = per;
-    g.NG = (per + G - 1) / G;
+    g.NG = (per + 7) / 8;
     g.G = (per + g.NG - 1) / g.NG;
     g.ZB = (planes + 7) / 8;
     const int row = lanes / rows, gl = g.G * bs;
@@ -404,6 +412,10 @@ __device__ __forceinline__ double lat_res_surface(const Lat<T>& L, int X, int Y,
 // being stored by a pass of their own: a parity launch then moves 5.5 values
 // per vertex (p, half of u read, of f read, of u written) instead of 4.5, and
 // the 10 values of that pass are gone.  PZ: p = 0 (the iterate starts at 0).
+// A lane takes two vertices of a row that are four apart: their taps are pairs of
+// consecutive entries.  Bound by L2 requests: 17 M vertices, FP64 209 us (3.6 TB/s
+// of its 5.5 values), 2.1 M vertices 19.2 us, a level of up to 36 thousand 3.4 us
+// (launch and two dependent loads).
 // ---------------------------------------------------------------------------
 template <typename T, int KIND, int NC, bool PZ>
 __global__ void __launch_bounds__(256) k_lat_vel(Lat<T> L, LatSurf B, int col, int sb, LatGrid tg,
@@ -530,7 +542,10 @@ __host__ __device__ __forceinline__ int lat_sub(int j, int Qp) { return lat_slot
 // ---------------------------------------------------------------------------
 // s = B u - g on every pressure row with the pressure update of the colour set
 // col: p += omega (s - C p) / C_xx on its vertices.  s is stored for the
-// vertices that a later sweep relaxes (all of them with ALL).
+// vertices that a later sweep relaxes (all of them with ALL).  A lane takes a quad
+// of consecutive vertices, one window of 36 values per field.  Bound by L2
+// requests, a quarter of them by the box's surface, whose lanes read 52 taps each
+// (2.1 M vertices, FP64: 40 us, without the surface 29); 17 M vertices 340 us.
 // ---------------------------------------------------------------------------
 template <typename T, int KIND, int NC>
 __global__ void __launch_bounds__(256) k_lat_bp(Lat<T> L, LatSurf B, int col, int sb, LatGrid tg,
@@ -596,7 +611,8 @@ __global__ void __launch_bounds__(256) k_lat_bp(Lat<T> L, LatSurf B, int col, in
         if ((all || (j & cm) != s0) && (j > 0 || P.q > 0)) st1(sx, at + lat_sub(j, Qp), s[j]);
 }
 
-// pressure sweep of one parity or colour: p += omega (s - C p) / C_xx
+// pressure sweep of one parity or colour: p += omega (s - C p) / C_xx.  Bound by
+// HBM: 17 M vertices, FP64 61 us, 4.5 TB/s of its 2 values per vertex.
 template <typename T, int KIND, int NC>
 __global__ void __launch_bounds__(256) k_lat_pres(Lat<T> L, LatSurf B, int col, int sb, LatGrid tg,
                                                   const T* __restrict__ sx, T* __restrict__ p, T omega) {
@@ -649,7 +665,9 @@ __global__ void __launch_bounds__(256) k_lat_pres(Lat<T> L, LatSurf B, int col, 
 // ---------------------------------------------------------------------------
 // r = b - K x (Dirichlet velocity rows 0); AP: r = K x instead.  WR: r is stored; NRM: per-block
 // partial sums of r^2 at partials[tile] (volume) and partials[total + block]
-// (surface), independent of the workgroup order.
+// (surface), independent of the workgroup order.  200 VGPRs leave two waves per
+// SIMD; held to three it spills and takes 746 us instead of 655 (17 M vertices,
+// FP64, written: 2.5 TB/s of 12 values; norm only 440 us).
 // ---------------------------------------------------------------------------
 template <typename T, int KIND, bool WR, bool NRM, bool AP = false>
 __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, LatGrid tg,
@@ -1131,7 +1149,8 @@ __global__ void __launch_bounds__(256) k_lat_ares(Lat<T> L, LatSurf B, int sb, L
 // ---------------------------------------------------------------------------
 // Restriction bc = P^T rf (weights 1 and 1/2, Dirichlet velocity rows 0), with
 // the coarse iterate xc set to 0 in the same pass.  Interior lanes: the coarse
-// quad q reads the fine row segments 8 q - 1 .. 8 q + 7 as pairs.
+// quad q reads the fine row segments 8 q - 1 .. 8 q + 7 as pairs.  17 M fine
+// vertices, FP64: 170 us, 3.7 TB/s of its bytes.
 // ---------------------------------------------------------------------------
 template <typename T, int NF = 4>
 __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSurf B, int sb, LatGrid tg,
@@ -1203,7 +1222,8 @@ __global__ void __launch_bounds__(256) k_lat_restrict(Lat<T> C, Lat<T> F, LatSur
 
 // Prolongation over every fine vertex: x_f += P e_c (SET: x_f = P e_c except on
 // Dirichlet velocity).  A fine vertex with odd bits d is the midpoint of the
-// coarse vertices (X - d) / 2 and (X + d) / 2.
+// coarse vertices (X - d) / 2 and (X + d) / 2.  17 M fine vertices, FP64: 248 us,
+// 4.7 TB/s of its bytes.
 template <typename T, bool SET, int NF = 4>
 __global__ void __launch_bounds__(256) k_lat_prolong(Lat<T> F, Lat<T> C, const T* __restrict__ ec,
                                                      T* __restrict__ xf) {
@@ -1279,7 +1299,8 @@ __global__ void __launch_bounds__(256) k_lat_mass(Lat<T> L, const T* __restrict_
 
 // Conversions between the ABI's per-macro layout (4 fields of stride plen) and
 // the lattice layout.  In: one lane per lattice vertex, from its primary slot.
-// Out: one lane per slot (every copy is written; padding untouched).
+// Out: one lane per slot (every copy is written; padding untouched).  17 M vertices,
+// FP64: 0.71 ms each, bound by the scattered side (64 lines per wave and field).
 template <typename T>
 __global__ void __launch_bounds__(256) k_lat_in(Lat<T> L, const int* __restrict__ node_slot,
                                                 const double* __restrict__ v, size_t plen,
