@@ -21,7 +21,7 @@
 //
 // Measured against the per-macro kernels on 17 M vertices, FP64, red-black: an
 // Uzawa step took 527 (f - B^T p with the red update) + 2 x 240 + 433 + 86 us and
-// takes 3 x 195 + 274 + 61 us; the residual 679 and 655 us, restriction 258 and
+// takes 3 x 176 + 265 + 61 us; the residual 679 and 655 us, restriction 258 and
 // 170, prolongation 431 and 248.  A solve pays the conversions at its ends, 0.71 ms
 // each.  Below 2 M vertices a launch takes 3 to 10 us whatever it computes: there
 // the gain is in launches (no f - B^T p pass, the visits) and in shorter chains of
@@ -774,8 +774,9 @@ __global__ void __launch_bounds__(256) k_lat_res(Lat<T> L, LatSurf B, int sb, La
 // read 20 (the five rows of A and C).  Rows past the box (a side has an odd number
 // of interior rows) are clamped into it; what they give is not stored.  Parities
 // are constants: y0 + z0 is even.  17 M vertices, FP64 / FP32: the velocity sweep
-// 209 -> 195 / 127 -> 104 us (3.8 / 3.6 TB/s of the bytes it cannot do without),
-// B u with the red pressures 340 -> 274 / 222 -> 178 us; at 2.1 M vertices the 512
+// 209 -> 176 / 127 -> 91 us (4.2 / 4.1 TB/s of the bytes it cannot do without),
+// B u with the red pressures 340 -> 265 / 222 -> 157 us (its neighbours' planes come
+// from HBM twice: 5 TB/s of traffic); at 2.1 M vertices the 512
 // workgroups leave the chip half empty (19.2 -> 21.7 and 40.3 -> 42.0 us, FP64), hence
 // the rule of eight workgroups per CU.  The residual (k_lat_res) lost in this form:
 // its 64 sums leave two waves per SIMD (448 -> 590 us).
@@ -887,6 +888,20 @@ __device__ __forceinline__ void lat_rows(P& blk, F&& body) {
     LAT_ROWS(1, 2);
 #undef LAT_ROWS
 }
+// Values that a launch touches once, right-hand sides and results, do not take L2
+// from the rows that its blocks share (nontemporal).  17 M vertices, FP64 / FP32:
+// the sweep 195 -> 176 / 104 -> 91 us, B u 274 -> 265 / 178 -> 157 us.  The one-row
+// kernels lose by it, at every size: the sweep 19.3 -> 26.5 us and B u 40 -> 48 us
+// at 2.1 M vertices (the next launch finds its data in L2), the prolongation 249 ->
+// 307 us at 17 M; the residual does not change.
+template <typename T>
+__device__ __forceinline__ T lat_once(const T* p) {
+    return __builtin_nontemporal_load(p);
+}
+template <typename T>
+__device__ __forceinline__ void lat_once(T* p, T v) {
+    __builtin_nontemporal_store(v, p);
+}
 // the value is worked out here, not where it is (conditionally) stored
 template <typename T>
 __device__ __forceinline__ void lat_pin(T& v) {
@@ -938,7 +953,8 @@ __global__ void __launch_bounds__(256, 4) k_lat_vel_blk(Lat<T> L, LatSurf B, int
         for (int k = 0; k < 3; ++k)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
-                t[o][k][e] = *P.template at<(o & 1), (o >> 1)>(L, b + k * len, lat_sub(lat_first(COL, o) + 2 * e, Qp));
+                t[o][k][e] =
+                    lat_once(P.template at<(o & 1), (o >> 1)>(L, b + k * len, lat_sub(lat_first(COL, o) + 2 * e, Qp)));
     });
     if (!PZ)
         lat_rows<6>(P, [&](auto dyc, auto dzc) __attribute__((always_inline)) {
@@ -992,7 +1008,7 @@ __global__ void __launch_bounds__(256, 4) k_lat_vel_blk(Lat<T> L, LatSurf B, int
             for (int h = 0; h < 2; ++h) {
                 const int j = lat_first(COL, o) + 2 * h;
                 if (j == 0 && P.q == 0) continue;   // x = 0
-                *P.template at<(o & 1), (o >> 1)>(L, x + k * len, lat_sub(j, Qp)) = t[o][k][h] * L.inva;
+                lat_once(P.template at<(o & 1), (o >> 1)>(L, x + k * len, lat_sub(j, Qp)), t[o][k][h] * L.inva);
             }
         });
     }
@@ -1021,7 +1037,7 @@ __global__ void __launch_bounds__(256, 4) k_lat_bp_blk(Lat<T> L, LatSurf B, int 
     lat_four([&](auto oc) __attribute__((always_inline)) {
         constexpr int o = decltype(oc)::value;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s[o][j] = -*P.template at<(o & 1), (o >> 1)>(L, g, lat_sub(j, Qp));
+        for (int j = 0; j < 4; ++j) s[o][j] = -lat_once(P.template at<(o & 1), (o >> 1)>(L, g, lat_sub(j, Qp)));
     });
 #pragma unroll 1
     for (int k = 0; k < 3; ++k) {
@@ -1078,9 +1094,9 @@ __global__ void __launch_bounds__(256, 4) k_lat_bp_blk(Lat<T> L, LatSurf B, int 
             if (j == 0 && P.q == 0) continue;   // x = 0
             const bool red = ((j + lat_first(0, o)) & 1) == 0;
             if (red)
-                *P.template at<(o & 1), (o >> 1)>(L, p, lat_sub(j, Qp)) =
-                    p0[o][j / 2] + omega * (s[o][j] - cp[o][j / 2]) * L.invc;
-            if (!red || all) *P.template at<(o & 1), (o >> 1)>(L, sx, lat_sub(j, Qp)) = s[o][j];
+                lat_once(P.template at<(o & 1), (o >> 1)>(L, p, lat_sub(j, Qp)),
+                         p0[o][j / 2] + omega * (s[o][j] - cp[o][j / 2]) * L.invc);
+            if (!red || all) lat_once(P.template at<(o & 1), (o >> 1)>(L, sx, lat_sub(j, Qp)), s[o][j]);
         }
     });
 }
