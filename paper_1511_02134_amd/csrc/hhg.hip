@@ -504,9 +504,12 @@ size_t layout(hhg_ctx* c, char* ws) {
         }
     }
     // the lattice's Krylov vectors share the memory of the per-macro ones: the
-    // ten vectors are contiguous up to their alignment, one more is b64
+    // ten vectors are contiguous up to their alignment, one more is b64.  The
+    // velocity cycles of MINRES run in FP64 on every level: contexts with FP32
+    // cycles have no FP64 lattice vectors below the finest level and keep the
+    // per-macro path there
     for (int q = 0; q < KV_N; ++q) c->lkv[q] = nullptr;
-    if (lat && c->opts.krylov && lat_applies(c)) {
+    if (lat && c->opts.krylov && lat_applies(c) && !mixed) {
         const size_t v4 = 4 * lat_geometry<double>(c, c->L).len;
         double* base = c->kv[0];
         const size_t room = (size_t)(c->kv[KV_N - 1] - base) + 4 * (size_t)c->H[c->L].len;
@@ -3646,6 +3649,84 @@ bool check_level(const hhg_ctx* c, int l, std::string* err) {
     CK((int)h.ctiles.size() <= c->npartials, "gradient partials too small");
     return true;
 }
+// The work vectors of the solvers: every one that a path of this context takes
+// lies inside the workspace and overlaps none that is in use beside it.  layout()
+// is run once more on a copy with a made-up base (nothing is dereferenced).
+bool check_workspace(const hhg_ctx* c, std::string* err) {
+    const int l = c->L;
+    hhg_ctx t;
+    t.opts = c->opts;
+    t.mi = c->mi;
+    t.R = c->R;
+    t.L = c->L;
+    t.H = c->H;
+    t.CH = c->CH;
+    t.lat = c->lat;
+    char* const base = (char*)(uintptr_t)(1 << 20);
+    const size_t bytes = layout(&t, base);
+    CK(bytes == layout(&t, base) && (!c->ws || bytes <= c->ws_bytes), "workspace size");
+    std::vector<std::pair<const char*, const char*>> used;
+    bool ok = true;
+    auto take = [&](const void* p, size_t n) {
+        const char* q = (const char*)p;
+        ok = ok && q >= base && q + n <= base + bytes;
+        used.push_back({q, q + n});
+    };
+    auto disjoint = [&] {
+        std::sort(used.begin(), used.end());
+        for (size_t i = 1; i < used.size(); ++i) ok = ok && used[i - 1].second <= used[i].first;
+        used.clear();
+        return ok;
+    };
+    const bool mixed = t.opts.precision == 1;
+    // cycles of hhg_solve, hhg_vcycle and hhg_fmg
+    for (int q = 0; q <= t.L; ++q) {
+        const size_t v4 = 4 * (t.lat ? lat_geometry<double>(&t, q).len : (size_t)t.H[q].len);
+        const bool fp64 = !mixed || q == t.L;
+        if (t.lat) {
+            const LatLevel& g = t.G[q];
+            if (fp64)
+                for (double* p : {g.x64, g.b64, g.r64}) take(p, 8 * v4);
+            if (mixed)
+                for (float* p : {g.x32, g.b32, g.r32}) take(p, 4 * v4);
+        } else {
+            const DevLevelArrays& a = t.A[q];
+            if (q < t.L && !mixed)
+                for (double* p : {a.x64, a.b64}) take(p, 8 * v4);
+            for (double* p : {a.r64, a.t64}) take(p, 8 * v4);
+            if (mixed)
+                for (float* p : {a.x32, a.b32, a.r32, a.t32}) take(p, 4 * v4);
+        }
+    }
+    CK(disjoint(), "vectors of the solver's cycles");
+    // velocity cycles in the per-macro layout (hhg_vel_cycle, hhg_scg), and the
+    // Krylov vectors beside them
+    for (int q = 0; q <= t.L; ++q) {
+        const size_t v4 = 4 * (size_t)t.H[q].len;
+        const DevLevelArrays& a = t.A[q];
+        if (q < t.L)
+            for (double* p : {a.x64, a.b64}) take(p, 8 * v4);
+        take(a.r64, 8 * v4);
+        if (t.opts.krylov && q == t.L)
+            for (double* p : t.kv) take(p, 8 * v4);
+    }
+    CK(disjoint(), "vectors of the velocity cycles");
+    // MINRES on the lattice
+    if (t.lkv[0]) {
+        for (int q = 0; q <= t.L; ++q) {
+            const size_t v4 = 4 * lat_geometry<double>(&t, q).len;
+            const LatLevel& g = t.G[q];
+            take(g.x64, 8 * v4);
+            take(g.r64, 8 * v4);
+            if (q < t.L) take(g.b64, 8 * v4);
+            if (q == t.L)
+                for (double* p : t.lkv) take(p, 8 * v4);
+        }
+        CK(disjoint(), "vectors of MINRES on the lattice");
+    }
+    return true;
+}
+
 #undef CK
 
 }  // namespace
@@ -3653,6 +3734,7 @@ bool check_level(const hhg_ctx* c, int l, std::string* err) {
 extern "C" hhg_status hhg_check_layout(const hhg_ctx* c) {
     if (!c) return fail(nullptr, HHG_EINVAL, "context is NULL");
     std::string err;
+    if (!check_workspace(c, &err)) return fail(const_cast<hhg_ctx*>(c), HHG_EINVAL, err);
     for (int l = 0; l <= c->L; ++l)
         if (!check_level(c, l, &err)) return fail(const_cast<hhg_ctx*>(c), HHG_EINVAL, err);
     return HHG_OK;
