@@ -59,6 +59,8 @@ inline int iface_blocks(int count) { return ((count + TPB - 1) / TPB + 7) / 8 * 
 // surface blocks of a lattice launch with bs lanes each, a multiple of 8 (the
 // volume tiles keep their XCD)
 inline int lat_sblocks(const LatSurf& B, int bs) { return ((B.beg[6] + bs - 1) / bs + 7) / 8 * 8; }
+// of a velocity launch: a lane for each component
+inline int lat_vel_sblocks(const LatSurf& B, int bs) { return ((3 * B.beg[6] + bs - 1) / bs + 7) / 8 * 8; }
 
 struct Carver {
     char* base;
@@ -1781,13 +1783,13 @@ void lat_vel(hhg_ctx* c, int l, int col, bool pz, int cls, T* x, const T* b, hip
     const LatVecs<T> v = lat_vecs<T>(c, l);
     const bool rb = c->opts.ordering == 2;
     const LatGrid tg = lat_grid(lat_pair_lanes(v.G, rb ? 2 : 1), v.G.ny - 2, v.G.nz - 2, lat_bs(v.G));
-    const int sb = lat_sblocks(v.g.svel, tg.bs);
+    const int sb = lat_vel_sblocks(v.g.svel, tg.bs);
     const dim3 grid(sb + tg.total), blk(tg.bs);
     ops(c, l, rb ? 0.5 : 0.25, 0, 0, 0);
     Timed tm(c, cls, s, l == c->L, rb ? c->lbytes_vel[col] + c->lbytes_vel[col + 2] : c->lbytes_vel[col]);
     if (rb && lat_blocks(c, v.G)) {
         const LatGrid bg = lat_block_grid(v.G, 0);
-        const int bsb = lat_sblocks(v.g.svel, bg.bs);
+        const int bsb = lat_vel_sblocks(v.g.svel, bg.bs);
         const dim3 g2(bsb + bg.total), b2(bg.bs);
         if (col == 0 && pz)
             hipLaunchKernelGGL((k_lat_vel_blk<T, 0, true>), g2, b2, 0, s, v.G, v.g.svel, bsb, bg, b, x);

@@ -326,26 +326,50 @@ __host__ __device__ __forceinline__ void lat_x_offsets(int s, int Qp, int* P, in
     *M = (lat_slot((s + 3) & 3) - here) * Qp - (s == 0 ? 1 : 0);
 }
 
-// Surface lanes of the passes: whole records, taps by address.
+// Surface lanes of the velocity launches: lane 3 i + k takes component k of vertex
+// i (its neighbour lanes read the same pressure taps).  Bound by latency, that of the
+// record index and then the record: the rows of B^T come from the vertex's class
+// instead, beside it, and every load is issued before the first use.  With a lane
+// per vertex that took the components one after another (its stores kept the next
+// one's loads back) a launch waited on these lanes: four cycles on 65 x 257 x 65
+// vertices with outflow through a side of 257 x 65, colour order, FP64, 11.0 -> 7.9
+// ms; 129^3 vertices, outflow, 12.5 -> 9.8 ms.
 template <typename T, bool PZ>
 __device__ __forceinline__ void lat_vel_surface(const Lat<T>& L, const LatSurf& B, int S, int col, int idx,
                                                 const T* __restrict__ b, T* __restrict__ x) {
     const size_t len = L.len;
+    const int i = idx / 3, k = idx - 3 * i;
     int X, Y, Z;
-    if (!lat_surf_lane(L, B, S, col, idx, &X, &Y, &Z)) return;
+    if (!lat_surf_lane(L, B, S, col, i, &X, &Y, &Z)) return;
     const int id = L.rid[lat_rid_index(L, X, Y, Z)];
-    if (L.rdir[id]) return;
-    const T* __restrict__ r = L.rec + (size_t)id * LR_SIZE;
     int nb[15];
     lat_taps(L, X, Y, Z, nb);
-    for (int k = 0; k < 3; ++k) {
-        T acc = b[k * len + nb[0]];
-        if (!PZ)
-            for (int g = 0; g < 15; ++g) acc -= r[LR_BT + 15 * k + g] * x[3 * len + nb[g]];
-        for (int g = 1; g < 7; ++g) acc -= r[LR_A + g] * x[k * len + nb[g]];
-        x[k * len + nb[0]] = acc * r[LR_INVA];
+    T* __restrict__ u = x + k * len;
+    T acc = b[k * len + nb[0]], v[15], w[15], n[7], a[7];
+    if (!PZ) {
+        const T* __restrict__ p = x + 3 * len;
+        const T* __restrict__ cr = L.cls + (size_t)lat_class(L, X, Y, Z) * LC_SIZE + LC_BT + 15 * k;
+#pragma unroll
+        for (int g = 0; g < 15; ++g) v[g] = p[nb[g]];
+#pragma unroll
+        for (int g = 0; g < 15; ++g) w[g] = cr[g];
     }
+#pragma unroll
+    for (int g = 1; g < 7; ++g) n[g] = u[nb[g]];
+    const bool dir = L.rdir[id] != 0;
+    const T* __restrict__ r = L.axr + (size_t)id * LX_SIZE;
+#pragma unroll
+    for (int g = 0; g < 7; ++g) a[g] = r[LX_A + g];   // the six taps, 1 / centre
+    __builtin_amdgcn_sched_barrier(0);
+    if (dir) return;
+    if (!PZ)
+#pragma unroll
+        for (int g = 0; g < 15; ++g) acc -= w[g] * v[g];
+#pragma unroll
+    for (int g = 1; g < 7; ++g) acc -= a[g - 1] * n[g];
+    u[nb[0]] = acc * a[LX_INVA];
 }
+// The surface lanes of the other passes: whole records, taps by address.
 template <typename T>
 __device__ __forceinline__ void lat_bp_surface(const Lat<T>& L, int X, int Y, int Z, int cm, int col,
                                                const T* __restrict__ g, T* __restrict__ x,
