@@ -1221,17 +1221,25 @@ inline int full_vblocks(int mode, int n_vtiles) {
 // and the interface blocks of K x and the residual separately: the volume
 // kernel is then not held to the interface lanes' register budget
 constexpr int SPLIT_MIN_N = 64;
-// general meshes (one vertex per lane below SPLIT_MIN_N too).  A shell of 480
-// macros, the residual with one launch / with two: n = 8 27 / 38 us, n = 16
-// 69 / 61 us, n = 32 168 / 136 us
-constexpr int SPLIT_MIN_N_GEN = 16;
+// general meshes (one vertex per lane below SPLIT_MIN_N too): from 16 intervals on
+// and ten volume tiles for each of the 256 CUs.  With fewer the chip is not full, and
+// a second launch costs more than the registers give.  K x with one launch / with two,
+// us: n = 16, 6 macros 10 / 15, 48 macros 19 / 27, 192 macros (2496 tiles) 48 / 49,
+// 480 macros (6240 tiles; the residual) 69 / 61; n = 32, 6 macros 11 / 17, 36 macros
+// 32 / 37, 72 macros (2088 tiles) 62 / 62, 108 macros (3132 tiles) 98 / 84, 480 macros
+// (the residual) 168 / 136; n = 8, 480 macros (2400 tiles; the residual) 27 / 38
+constexpr int SPLIT_MIN_N_GEN = 16, SPLIT_MIN_TILES_GEN = 2560;
+template <typename T, bool GEN>
+bool kx_split(const LevelDev<T>& v) {
+    return v.n >= SPLIT_MIN_N || (GEN && v.n >= SPLIT_MIN_N_GEN && v.n_vtiles >= SPLIT_MIN_TILES_GEN);
+}
 
 // K x or the residual (MODE_APPLY / MODE_RES); MIRROR: interface taps from
 // the level's mirror of x
 template <typename T, int MODE, bool MIRROR, bool DOP, bool GEN>
 void launch_kx_op(LevelDev<T>& v, int ib, const T* x, const T* b, T* y, double* partials,
                   hipStream_t s) {
-    if (v.n >= (GEN ? SPLIT_MIN_N_GEN : SPLIT_MIN_N)) {
+    if (kx_split<T, GEN>(v)) {
         if constexpr (DOP || GEN) {
             // volume launch: one vertex per lane (four blocks per tile)
             hipLaunchKernelGGL((k_full<T, MODE, false, MIRROR, false, 1, DOP, GEN>),
