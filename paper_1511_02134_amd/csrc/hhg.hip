@@ -2891,13 +2891,15 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
     hhg_ctx::CycleGraph* graph = (c->opts.graphs && max_cycles > 0 && !c->timing && !c->phase_timing)
                                      ? cycle_graph(c, xs, bs, body)
                                      : nullptr;
+    hipError_t he = hipSuccess;
     for (k = 1; k <= max_cycles; ++k) {
         if (graph)
-            HIPCHECK(c, replay(c, graph, s));
+            he = replay(c, graph, s);
         else
             body(s);
-        HIPCHECK(c, hipMemcpyAsync(&nrm, c->scal, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHECK(c, hipStreamSynchronize(s));
+        if (he == hipSuccess) he = hipMemcpyAsync(&nrm, c->scal, sizeof(double), hipMemcpyDeviceToHost, s);
+        if (he == hipSuccess) he = hipStreamSynchronize(s);
+        if (he != hipSuccess) break;
         I->res_hist[k] = nrm;
         I->cycles = k;
         I->r_final = nrm;
@@ -2918,7 +2920,12 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
         if (stagn >= 5) break;
     }
     c->phase_active = false;
+    // also after a failed call: x holds the cycles done
     if (lat) lat_out(c, c->L, xs, x, s);
+    if (he != hipSuccess) {
+        I->status = HHG_EDEVICE;
+        return fail(c, HHG_EDEVICE, std::string("solver cycle: ") + hipGetErrorString(he));
+    }
     if (e1) (void)hipEventRecord(e1, s);
     if (e0 && e1) {
         (void)hipEventSynchronize(e1);
@@ -3858,6 +3865,11 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
     double h[3];
     hhg_status rs = read_scalars(c, h, c->kscal, 3, s);
     if (rs != HHG_OK) return rs;
+    // after a failed call x holds the iterations done
+    auto leave = [&] {
+        if (lat) lat_out(c, L, x, xc, s);
+        return rs;
+    };
     const double r0 = h[2];
     I->r0 = r0;
     hist_put(I, 0, r0);
@@ -3883,7 +3895,7 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
                            (const double*)Vb[cur], Vb[cur ^ 1], n4, beta,
                            it == 0 ? 0.0 : beta / beta_prev, (const double*)c->kscal);
         block_prec(c, nu, Vb[cur ^ 1], Zb[zc ^ 1], c->kscal + 1, s, lat);
-        if ((rs = read_scalars(c, h, c->kscal, 3, s)) != HHG_OK) return rs;
+        if ((rs = read_scalars(c, h, c->kscal, 3, s)) != HHG_OK) return leave();
         if (pending) {
             // residual of the previous update (Q, V and Z do not touch x or r)
             hist_put(I, it, h[2]);
@@ -3931,7 +3943,7 @@ hhg_status hhg_pminres(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_
         beta = beta_new;
     }
     if (pending) {
-        if ((rs = read_scalars(c, h, c->kscal + 2, 1, s)) != HHG_OK) return rs;
+        if ((rs = read_scalars(c, h, c->kscal + 2, 1, s)) != HHG_OK) return leave();
         hist_put(I, it, h[0]);
         if (!std::isfinite(h[0]))
             st = HHG_ENAN;
