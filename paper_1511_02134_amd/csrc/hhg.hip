@@ -107,8 +107,8 @@ struct LatLevel {
     unsigned char* rdir = nullptr;
     double* cls64 = nullptr;
     float* cls32 = nullptr;
-    double *rec64 = nullptr, *axr64 = nullptr, *x64 = nullptr, *b64 = nullptr, *r64 = nullptr;
-    float *rec32 = nullptr, *axr32 = nullptr, *x32 = nullptr, *b32 = nullptr, *r32 = nullptr;
+    double *x64 = nullptr, *b64 = nullptr, *r64 = nullptr;
+    float *x32 = nullptr, *b32 = nullptr, *r32 = nullptr;
     int nrec = 0, nrid = 0;
     LatSurf svel, spres, sring;   // surface lanes of velocity, pressure and full launches
     // one-workgroup visits (k_lat_visit): 0 no, otherwise the variant
@@ -145,6 +145,8 @@ struct hhg_ctx {
     std::vector<LatLevel> G;
     std::vector<Lat<double>> G64;
     std::vector<Lat<float>> G32;
+    double* lat_rec64 = nullptr;   // records of all levels (lat_records)
+    float* lat_rec32 = nullptr;
     uint8_t* lat_owned = nullptr;  // finest level: 1 on vertices (padding 0)
     double* lat_pinv = nullptr;    // and the pressure preconditioner
     double* lkv[KV_N] = {};        // Krylov vectors in the lattice layout, or null
@@ -303,6 +305,11 @@ bool lat_reserved(const hhg_ctx* c) {
     const int64_t tiles = ((int64_t)h.lat[1] * G.Qi / 256 + 1) * h.lat[2];
     return plane < lim && tiles < lim && (int64_t)G.RS * G.ny * G.nz < (1LL << 29) - 64 && h.lat[2] < 65536;
 }
+
+// values of a level's records: the surface records, then the axis records, each
+// from a line's start in FP32 too
+inline size_t lat_axis_records(int nrec) { return ((size_t)nrec * LR_SIZE + 31) / 32 * 32; }
+inline size_t lat_records(int nrec) { return lat_axis_records(nrec) + ((size_t)nrec * LX_SIZE + 31) / 32 * 32; }
 
 // Lanes per workgroup: levels with fewer than 2048 full waves of work spread
 // them one wave to a workgroup over the CUs (a launch there waits on the loads
@@ -483,8 +490,6 @@ size_t layout(hhg_ctx* c, char* ws) {
             g.nrid = (c->mi.ext[0] + 1) * (c->mi.ext[1] + 1) * (c->mi.ext[2] + 1) * LPAT;
             g.rid = cv.take<int>(g.nrid);
             g.rdir = cv.take<unsigned char>(g.nrec);
-            g.rec64 = cv.take<double>((size_t)g.nrec * LR_SIZE);
-            g.axr64 = cv.take<double>((size_t)g.nrec * LX_SIZE);
             g.cls64 = cv.take<double>(27 * LC_SIZE);
             if (mixed) g.cls32 = cv.take<float>(27 * LC_SIZE);
             const size_t v4 = 4 * G.len;
@@ -494,8 +499,6 @@ size_t layout(hhg_ctx* c, char* ws) {
                 g.r64 = cv.take<double>(v4);
             }
             if (mixed) {
-                g.rec32 = cv.take<float>((size_t)g.nrec * LR_SIZE);
-                g.axr32 = cv.take<float>((size_t)g.nrec * LX_SIZE);
                 g.x32 = cv.take<float>(v4);
                 g.b32 = cv.take<float>(v4);
                 g.r32 = cv.take<float>(v4);
@@ -504,6 +507,11 @@ size_t layout(hhg_ctx* c, char* ws) {
                                                 lat_sblocks(g.sring, lat_bs(G)));
             maxblocks = std::max(maxblocks, ((G.Qi + 1) * G.ny + 255) / 256 * G.nz);
         }
+        // the records of all levels in one block: a new viscosity is one copy
+        size_t all = 0;
+        for (int l = 0; l < nl; ++l) all += lat_records(c->G[l].nrec);
+        c->lat_rec64 = cv.take<double>(all);
+        c->lat_rec32 = mixed ? cv.take<float>(all) : nullptr;
     }
     // the lattice's Krylov vectors share the memory of the per-macro ones: the
     // ten vectors are contiguous up to their alignment, one more is b64.  The
@@ -636,43 +644,108 @@ hhg_status coarse_direct_setup(hhg_ctx* c) {
     return HHG_OK;
 }
 
-// Records and constants of the lattice path (with every change of viscosity).
+// What the lattice path knows of a level besides its records, none of it dependent
+// on the viscosity: the record of every pattern (lat_rid_index), whether a record's
+// velocity is Dirichlet, and the rows of B and B^T by surface class.  The vertices
+// with offsets 0..3 in every cell show each pattern.
+struct LatTables {
+    std::vector<int> rid;
+    std::vector<unsigned char> dir;
+    std::vector<double> cls;
+};
+const double* lat_record(const HostLevel& h, int r) {
+    return r < h.nm ? &h.st_vol_global[(size_t)r * ST_SIZE] : &h.st[(size_t)r * ST_SIZE];
+}
+LatTables lat_tables(const hhg_ctx* c, int l) {
+    const HostLevel& h = c->H[l];
+    const Lat<double> G = lat_geometry<double>(c, l);
+    LatTables t{std::vector<int>(c->G[l].nrid, 0), std::vector<unsigned char>(c->G[l].nrec, 0),
+                std::vector<double>(27 * LC_SIZE, 0.0)};
+    const int* ext = c->mi.ext;
+    const int rows[3] = {4 * (ext[0] + 1), 4 * (ext[1] + 1), 4 * (ext[2] + 1)};
+    for (int iz = 0; iz < rows[2]; ++iz)
+        for (int iy = 0; iy < rows[1]; ++iy)
+            for (int ix = 0; ix < rows[0]; ++ix) {
+                const int X = (ix >> 2) * h.n + (ix & 3), Y = (iy >> 2) * h.n + (iy & 3),
+                          Z = (iz >> 2) * h.n + (iz & 3);
+                if (X >= G.nx || Y >= G.ny || Z >= G.nz) continue;
+                const int64_t v = X + (int64_t)G.nx * (Y + (int64_t)G.ny * Z);
+                const int r = h.node_sid[v] < 0 ? -h.node_sid[v] - 1 : h.node_sid[v];
+                t.rid[lat_rid_index(G, X, Y, Z)] = r;
+                if (h.node_dir[v]) t.dir[r] = 1;
+                double* cr = &t.cls[(size_t)lat_class(G, X, Y, Z) * LC_SIZE];
+                std::copy_n(lat_record(h, r) + ST_B, 45, cr + LC_B);
+                std::copy_n(lat_record(h, r) + ST_BT, 45, cr + LC_BT);
+            }
+    return t;
+}
+
+// The lattice path's tables, once at creation.
+hhg_status upload_lattice_tables(hhg_ctx* c) {
+    if (!c->lat) return HHG_OK;
+    hhg_status s;
+    {
+        // the level-0 tables in the lattice layout: one copy per vertex
+        const CoarseHost& C = c->CH;
+        const Lat<double> G = lat_geometry<double>(c, 0);
+        std::vector<int32_t> slot(C.N), cptr(C.N + 1);
+        for (int v = 0; v < C.N; ++v) {
+            const int nd = C.node_lat[v];
+            slot[v] = lat_at(G, nd % G.nx, nd / G.nx % G.ny, nd / (G.nx * G.ny));
+            cptr[v] = v;
+        }
+        cptr[C.N] = C.N;
+        if ((s = upload<int32_t>(c, (int32_t*)c->cdl.node_slot, slot.data(), slot.size())) != HHG_OK) return s;
+        if ((s = upload<int32_t>(c, (int32_t*)c->cdl.node_cptr, cptr.data(), cptr.size())) != HHG_OK) return s;
+    }
+    for (int l = 0; l <= c->L; ++l) {
+        LatLevel& g = c->G[l];
+        const LatTables t = lat_tables(c, l);
+        if ((s = upload<int>(c, g.rid, t.rid.data(), t.rid.size())) != HHG_OK) return s;
+        if ((s = upload<unsigned char>(c, g.rdir, t.dir.data(), t.dir.size())) != HHG_OK) return s;
+        if ((s = upload<double>(c, g.cls64, t.cls.data(), t.cls.size())) != HHG_OK) return s;
+        if (!g.cls32) continue;
+        std::vector<float> c32(t.cls.begin(), t.cls.end());
+        if ((s = upload<float>(c, g.cls32, c32.data(), c32.size())) != HHG_OK) return s;
+    }
+    if (c->lkv[0]) {
+        const HostLevel& h = c->H[c->L];
+        const Lat<double> G = lat_geometry<double>(c, c->L);
+        std::vector<uint8_t> own(G.len, 0);
+        for (int z = 0; z < h.lat[2]; ++z)
+            for (int y = 0; y < h.lat[1]; ++y)
+                for (int x = 0; x < h.lat[0]; ++x) own[lat_at(G, x, y, z)] = 1;
+        if ((s = upload<uint8_t>(c, c->lat_owned, own.data(), own.size())) != HHG_OK) return s;
+        // the pressure preconditioner's padding; its vertices come with the stencils
+        const std::vector<double> zero(G.len, 0.0);
+        if ((s = upload<double>(c, c->lat_pinv, zero.data(), zero.size())) != HHG_OK) return s;
+    }
+    return HHG_OK;
+}
+
+// Its records and constants, with every change of viscosity.
 hhg_status lat_visit_setup(hhg_ctx* c);
 hhg_status upload_lattice(hhg_ctx* c) {
     if (!c->lat) return HHG_OK;
-    c->lat_kind = 0;
+    int kind = 0;
     for (const MacroInfo& m : c->mi.macros)
-        if (m.nu != c->mi.macros[0].nu) c->lat_kind = 1;
+        if (m.nu != c->mi.macros[0].nu) kind = 1;
+    // attributes of the visits' kernels: per kind
+    const bool setup = c->G64.empty() || kind != c->lat_kind;
+    c->lat_kind = kind;
     c->G64.assign(c->L + 1, Lat<double>{});
     c->G32.assign(c->L + 1, Lat<float>{});
-    {
-        const HostLevel& h = c->H[c->L];
-        const Lat<double> G = lat_geometry<double>(c, c->L);
-        std::vector<uint8_t> own(c->opts.krylov ? G.len : 0, 0);
-        std::vector<double> pinv(own.size(), 0.0);
-        if (!own.empty())
-            for (int64_t v = 0; v < h.N; ++v) {
-                const int row = (int)(v / G.nx), a = lat_at(G, (int)(v % G.nx), row % G.ny, row / G.ny);
-                const int32_t sid = h.node_sid[v];
-                const double* st = sid < 0 ? &h.st_vol_global[(size_t)(-sid - 1) * ST_SIZE]
-                                           : &h.st[(size_t)sid * ST_SIZE];
-                own[a] = 1;
-                pinv[a] = 1.0 / st[ST_MASSNU];
-            }
-        hhg_status s;
-        if ((s = upload<uint8_t>(c, c->lat_owned, own.data(), own.size())) != HHG_OK) return s;
-        if ((s = upload<double>(c, c->lat_pinv, pinv.data(), pinv.size())) != HHG_OK) return s;
-    }
+    hhg_status s;
+    size_t all = 0, off = 0;
+    for (const LatLevel& g : c->G) all += lat_records(g.nrec);
+    std::vector<double> recs(all, 0.0);
     for (int l = 0; l <= c->L; ++l) {
         const HostLevel& h = c->H[l];
         LatLevel& g = c->G[l];
         Lat<double> G = lat_geometry<double>(c, l);
-        std::vector<double> rec((size_t)g.nrec * LR_SIZE, 0.0), axr((size_t)g.nrec * LX_SIZE, 0.0);
-        std::vector<unsigned char> dir(g.nrec, 0);
-        std::vector<int> rid(g.nrid, 0);
-        std::vector<double> cls(27 * LC_SIZE, 0.0);
+        double *const rec = &recs[off], *const axr = rec + lat_axis_records(g.nrec);
         for (int r = 0; r < g.nrec; ++r) {
-            const double* st = r < h.nm ? &h.st_vol_global[(size_t)r * ST_SIZE] : &h.st[(size_t)r * ST_SIZE];
+            const double* st = lat_record(h, r);
             double* o = &rec[(size_t)r * LR_SIZE];
             for (int q = 0; q < 15; ++q) {
                 o[LR_A + q] = st[ST_A + q];
@@ -695,22 +768,6 @@ hhg_status upload_lattice(hhg_ctx* c) {
             a[LX_C0] = st[ST_C];
             a[LX_INVC] = st[ST_INVC];
         }
-        // the vertices with offsets 0..3 in every cell show each pattern
-        const int n = h.n;
-        for (int Z = 0; Z < G.nz; ++Z)
-            for (int Y = 0; Y < G.ny; ++Y)
-                for (int X = 0; X < G.nx; ++X) {
-                    if ((X & (n - 1)) > 3 || (Y & (n - 1)) > 3 || (Z & (n - 1)) > 3) continue;
-                    const int64_t v = X + (int64_t)G.nx * (Y + (int64_t)G.ny * Z);
-                    const int sid = h.node_sid[v] < 0 ? -h.node_sid[v] - 1 : h.node_sid[v];
-                    rid[lat_rid_index(G, X, Y, Z)] = sid;
-                    if (h.node_dir[v]) dir[sid] = 1;
-                    double* cr = &cls[(size_t)lat_class(G, X, Y, Z) * LC_SIZE];
-                    for (int q = 0; q < 45; ++q) {
-                        cr[LC_B + q] = rec[(size_t)sid * LR_SIZE + LR_B + q];
-                        cr[LC_BT + q] = rec[(size_t)sid * LR_SIZE + LR_BT + q];
-                    }
-                }
         // constants of the interior vertices (pair symmetries as in the
         // volume records)
         const double* st = &h.st_vol_global[0];
@@ -727,12 +784,6 @@ hhg_status upload_lattice(hhg_ctx* c) {
             for (int q = 0; q < 7; ++q)
                 G.bt[k][q] = 0.25 * (st[ST_BT + 15 * k + 2 * q + 1] - st[ST_BT + 15 * k + 2 * q + 2] -
                                      st[ST_B + 15 * k + 2 * q + 1] + st[ST_B + 15 * k + 2 * q + 2]);
-        hhg_status s;
-        if ((s = upload<int>(c, g.rid, rid.data(), rid.size())) != HHG_OK) return s;
-        if ((s = upload<unsigned char>(c, g.rdir, dir.data(), dir.size())) != HHG_OK) return s;
-        if ((s = upload<double>(c, g.rec64, rec.data(), rec.size())) != HHG_OK) return s;
-        if ((s = upload<double>(c, g.axr64, axr.data(), axr.size())) != HHG_OK) return s;
-        if ((s = upload<double>(c, g.cls64, cls.data(), cls.size())) != HHG_OK) return s;
         Lat<float> F = lat_geometry<float>(c, l);
         for (int q = 0; q < 3; ++q) {
             F.a[q] = (float)G.a[q];
@@ -746,23 +797,24 @@ hhg_status upload_lattice(hhg_ctx* c) {
         F.mass = (float)G.mass;
         G.rid = F.rid = g.rid;
         G.rdir = F.rdir = g.rdir;
-        G.rec = g.rec64;
-        G.axr = g.axr64;
-        F.rec = g.rec32;
-        F.axr = g.axr32;
+        G.rec = c->lat_rec64 + off;
+        G.axr = G.rec + lat_axis_records(g.nrec);
+        if (c->lat_rec32) {
+            F.rec = c->lat_rec32 + off;
+            F.axr = F.rec + lat_axis_records(g.nrec);
+        }
         G.cls = g.cls64;
         F.cls = g.cls32;
-        if (g.rec32) {
-            std::vector<float> c32(cls.begin(), cls.end());
-            if ((s = upload<float>(c, g.cls32, c32.data(), c32.size())) != HHG_OK) return s;
-            std::vector<float> r32(rec.begin(), rec.end()), a32(axr.begin(), axr.end());
-            if ((s = upload<float>(c, g.rec32, r32.data(), r32.size())) != HHG_OK) return s;
-            if ((s = upload<float>(c, g.axr32, a32.data(), a32.size())) != HHG_OK) return s;
-        }
         c->G64[l] = G;
         c->G32[l] = F;
+        off += lat_records(g.nrec);
     }
-    return lat_visit_setup(c);
+    if ((s = upload<double>(c, c->lat_rec64, recs.data(), recs.size())) != HHG_OK) return s;
+    if (c->lat_rec32) {
+        const std::vector<float> r32(recs.begin(), recs.end());
+        if ((s = upload<float>(c, c->lat_rec32, r32.data(), r32.size())) != HHG_OK) return s;
+    }
+    return setup ? lat_visit_setup(c) : HHG_OK;
 }
 
 hhg_status upload_stencils(hhg_ctx* c) {
@@ -813,22 +865,11 @@ hhg_status upload_stencils(hhg_ctx* c) {
         return s;
     c->cd.inv_mass = c->inv_mass[0];
     if (c->lat) {
-        // the level-0 tables in the lattice layout: one copy per vertex
-        const Lat<double> G = lat_geometry<double>(c, 0);
-        std::vector<int32_t> slot(C.N), cptr(C.N + 1);
-        for (int v = 0; v < C.N; ++v) {
-            const int nd = C.node_lat[v];
-            slot[v] = lat_at(G, nd % G.nx, nd / G.nx % G.ny, nd / (G.nx * G.ny));
-            cptr[v] = v;
-        }
-        cptr[C.N] = C.N;
         CoarseDev d = c->cd;
         d.node_slot = c->cdl.node_slot;
         d.node_copy = c->cdl.node_copy;
         d.node_cptr = c->cdl.node_cptr;
         c->cdl = d;
-        if ((s = upload<int32_t>(c, (int32_t*)d.node_slot, slot.data(), slot.size())) != HHG_OK) return s;
-        if ((s = upload<int32_t>(c, (int32_t*)d.node_cptr, cptr.data(), cptr.size())) != HHG_OK) return s;
         if ((s = upload_lattice(c)) != HHG_OK) return s;
     }
     {
@@ -846,6 +887,13 @@ hhg_status upload_stencils(hhg_ctx* c) {
             pinv[q] = 1.0 / rec[ST_MASSNU];
         }
         if ((s = upload<double>(c, c->A[c->L].pinv, pinv.data(), pinv.size())) != HHG_OK) return s;
+        if (c->lkv[0]) {
+            const Lat<double>& G = c->G64[c->L];
+            hipLaunchKernelGGL((k_lat_in<double, 1>), dim3((G.nx * G.ny + 255) / 256, G.nz), dim3(256), 0,
+                               (hipStream_t) nullptr, G, (const int*)c->A[c->L].node_slot,
+                               (const double*)c->A[c->L].pinv, (size_t)h.len, c->lat_pinv);
+            HIPCHECK(c, hipGetLastError());
+        }
     }
     return HHG_OK;
 }
@@ -947,6 +995,7 @@ hhg_status upload_all(hhg_ctx* c) {
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)dl) != hipSuccess))
             return fail(c, HHG_EDEVICE, "cannot raise the LDS limit of the direct coarse kernel");
     }
+    if ((s = upload_lattice_tables(c)) != HHG_OK) return s;
     if ((s = upload_stencils(c)) != HHG_OK) return s;
     {
         // primary-slot flags of the finest level (inner products count each
@@ -3338,21 +3387,26 @@ bool check_lattice(const hhg_ctx* c, int l, std::string* err) {
                 for (int x = 0; x < G.nx; ++x)
                     CK(seen[node(x, y, z)] == 1, "blocks do not cover the rows");
     }
-    // records: vertices with one index share their stencil record
-    std::vector<int> sid_of((size_t)g.nrid, INT32_MIN);
+    // tables: the record, Dirichlet flag and class rows of every vertex
+    const LatTables tab = lat_tables(c, l);
     for (int z = 0; z < G.nz; ++z)
         for (int y = 0; y < G.ny; ++y)
             for (int x = 0; x < G.nx; ++x) {
-                const int i = lat_rid_index(G, x, y, z);
+                const int i = lat_rid_index(G, x, y, z), sid = h.node_sid[node(x, y, z)];
                 CK(i >= 0 && i < g.nrid, "record index out of range");
-                const int sid = h.node_sid[node(x, y, z)];
-                const bool small = (x & (G.n - 1)) <= 3 && (y & (G.n - 1)) <= 3 && (z & (G.n - 1)) <= 3;
-                if (small) sid_of[i] = sid;
+                const int r = tab.rid[i];
+                CK(r == (sid < 0 ? -sid - 1 : sid), "record of another vertex");
+                CK(tab.dir[r] == (h.node_dir[node(x, y, z)] ? 1 : 0), "Dirichlet flag of a record");
+                if (!surface(x, y, z)) continue;
+                const double *cr = &tab.cls[(size_t)lat_class(G, x, y, z) * LC_SIZE], *st = lat_record(h, r);
+                double most = 0.0, off = 0.0;
+                for (int q = 0; q < 45; ++q) {
+                    most = std::max({most, std::fabs(st[ST_B + q]), std::fabs(st[ST_BT + q])});
+                    off = std::max({off, std::fabs(st[ST_B + q] - cr[LC_B + q]),
+                                    std::fabs(st[ST_BT + q] - cr[LC_BT + q])});
+                }
+                CK(off <= 1e-14 * most, "class rows of B and B^T");
             }
-    for (int z = 0; z < G.nz; ++z)
-        for (int y = 0; y < G.ny; ++y)
-            for (int x = 0; x < G.nx; ++x)
-                CK(sid_of[lat_rid_index(G, x, y, z)] == h.node_sid[node(x, y, z)], "record of another vertex");
     // prolongation into this level
     if (l > 0) {
         const Lat<double> C = lat_geometry<double>(c, l - 1);

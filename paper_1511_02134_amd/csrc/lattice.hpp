@@ -1341,7 +1341,7 @@ __global__ void __launch_bounds__(256) k_lat_mass(Lat<T> L, const T* __restrict_
 // the lattice layout.  In: one lane per lattice vertex, from its primary slot.
 // Out: one lane per slot (every copy is written; padding untouched).  17 M vertices,
 // FP64: 0.71 ms each, bound by the scattered side (64 lines per wave and field).
-template <typename T>
+template <typename T, int NF = 4>
 __global__ void __launch_bounds__(256) k_lat_in(Lat<T> L, const int* __restrict__ node_slot,
                                                 const double* __restrict__ v, size_t plen,
                                                 T* __restrict__ x) {
@@ -1350,7 +1350,7 @@ __global__ void __launch_bounds__(256) k_lat_in(Lat<T> L, const int* __restrict_
     if (y >= L.ny) return;
     const int s = node_slot[(size_t)(z * L.ny + y) * L.nx + X], a = lat_at(L, X, y, z);
 #pragma unroll
-    for (int f = 0; f < 4; ++f) x[f * L.len + a] = (T)v[f * plen + s];
+    for (int f = 0; f < NF; ++f) x[f * L.len + a] = (T)v[f * plen + s];
 }
 template <typename T>
 __global__ void __launch_bounds__(256) k_lat_out(Lat<T> L, const int* __restrict__ slot_node, size_t plen,
