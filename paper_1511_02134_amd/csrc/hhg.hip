@@ -398,6 +398,10 @@ size_t layout(hhg_ctx* c, char* ws) {
     const int nl = c->L + 1;
     c->A.assign(nl, DevLevelArrays{});
     const bool mixed = c->opts.precision == 1;
+    // the work vectors of the per-macro paths, level by level: no call uses them and
+    // those of the lattice cycles at once, and neither hold anything between calls
+    std::vector<Carver> shared(nl, Carver(ws));
+    std::vector<size_t> shared_end(nl, 0);
     int maxblocks = 1;
     for (int l = 0; l < nl; ++l) {
         HostLevel& h = c->H[l];
@@ -428,6 +432,7 @@ size_t layout(hhg_ctx* c, char* ws) {
         a.cx64 = cv.take<double>(c4);
         a.cx32 = mixed ? cv.take<float>(c4) : nullptr;
         const size_t v4 = 4 * (size_t)h.len;
+        const size_t work = cv.off;
         a.r64 = cv.take<double>(v4);
         a.t64 = cv.take<double>(v4);
         // corrections and right-hand sides of the coarser levels; on the finest
@@ -441,6 +446,9 @@ size_t layout(hhg_ctx* c, char* ws) {
             a.r32 = cv.take<float>(v4);
             a.t32 = cv.take<float>(v4);
         }
+        shared[l] = Carver(ws);
+        shared[l].off = work;
+        shared_end[l] = cv.off;
         a.hyb_list = cv.take<int32_t>(std::max<size_t>(1, h.hyb_list.size()));
         a.hyb_mask = cv.take<int32_t>(std::max<size_t>(1, h.hyb_mask.size()));
         a.snap64 = c->opts.ordering == 1 ? cv.take<double>((size_t)4 * std::max(1, h.nif)) : nullptr;
@@ -493,16 +501,19 @@ size_t layout(hhg_ctx* c, char* ws) {
             g.cls64 = cv.take<double>(27 * LC_SIZE);
             if (mixed) g.cls32 = cv.take<float>(27 * LC_SIZE);
             const size_t v4 = 4 * G.len;
-            if (!mixed || l == c->L) {
-                g.x64 = cv.take<double>(v4);
-                g.b64 = cv.take<double>(v4);
-                g.r64 = cv.take<double>(v4);
-            }
-            if (mixed) {
-                g.x32 = cv.take<float>(v4);
-                g.b32 = cv.take<float>(v4);
-                g.r32 = cv.take<float>(v4);
-            }
+            auto vec = [&](auto** p) {
+                using V = std::remove_reference_t<decltype(**p)>;
+                Carver in = shared[l];
+                *p = in.take<V>(v4);
+                if (in.off <= shared_end[l])
+                    shared[l] = in;
+                else
+                    *p = cv.take<V>(v4);
+            };
+            if (!mixed || l == c->L)
+                for (double** p : {&g.x64, &g.b64, &g.r64}) vec(p);
+            if (mixed)
+                for (float** p : {&g.x32, &g.b32, &g.r32}) vec(p);
             maxblocks = std::max(maxblocks, lat_quad_grid(G).total +
                                                 lat_sblocks(g.sring, lat_bs(G)));
             maxblocks = std::max(maxblocks, ((G.Qi + 1) * G.ny + 255) / 256 * G.nz);

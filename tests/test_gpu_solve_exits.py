@@ -39,7 +39,9 @@ def test_solve_without_cycles_reports_the_residual_and_leaves_x(R, opts):
     assert torch.equal(x, x0)
     y = x0.clone()
     a, c = s.solve(x, b, rtol=1e-8, max_cycles=3), t.solve(y, b, rtol=1e-8, max_cycles=3)
-    assert a["cycles"] == c["cycles"] and a["res_hist"] == c["res_hist"] and torch.equal(x, y)
+    assert a["cycles"] == c["cycles"] and a["res_hist"] == c["res_hist"]
+    # on every vertex (level 0 alone: the cycles leave anything in the padding)
+    assert torch.equal(s.gather(x), t.gather(y))
 
 
 # stands before the runtime in the symbol search order and returns an error from
