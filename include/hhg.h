@@ -297,8 +297,8 @@ hhg_status hhg_residual(hhg_ctx* ctx, int32_t level, const void* d_x, const void
  * all pressure rows) written to the device scalar *d_norm instead of host
  * memory.  It allocates nothing, records no event and never synchronises:
  * its per-block partial sums live in a static device array of the library
- * (32 MiB, one per GPU, held until the process ends); levels needing
- * more than 2^20 partial sums (beyond about 9 refinements of the
+ * (8 MiB, 2^20 doubles, one per GPU, held until the process ends); levels
+ * needing more partial sums than that (beyond about 9 refinements of the
  * unit cube) return HHG_EINVAL.  Every call on one GPU shares that array, so
  * calls that overlap in time on one GPU (on different streams or host
  * threads) race; calls ordered on one stream do not.  The context's device

@@ -25,10 +25,10 @@ using namespace hhg;
 // runs on holds its own copy until the process ends.  In host code the
 // array's name is not a device address: the address of the current device's
 // copy comes from hipGetSymbolAddress (scratch_address below).
-// Levels of up to 2^20 sums are taken, counted as one per tile below SPLIT_MIN_N
-// intervals; launches of one vertex per lane write four per tile there.
-constexpr size_t NOALLOC_MAX_PARTIALS = size_t(1) << 20;
-constexpr size_t NOALLOC_SCRATCH_DOUBLES = 4 * NOALLOC_MAX_PARTIALS;   // 32 MiB
+// Levels below SPLIT_MIN_N intervals always fit, at four sums per tile too: a macro
+// has a vertex of its own on level 0, whose 16384 unknowns hold at most 4096 macros,
+// and at 32 intervals 29 tiles and 8 blocks of interface vertices.
+constexpr size_t NOALLOC_SCRATCH_DOUBLES = size_t(1) << 20;   // 8 MiB
 static __device__ __align__(256) double scratch[NOALLOC_SCRATCH_DOUBLES];
 
 namespace {
@@ -2652,11 +2652,11 @@ hhg_status hhg_residual_noalloc(hhg_ctx* c, int32_t l, const void* x, const void
     if (hipGetDevice(&dev) != hipSuccess || dev != c->dev)
         return fail(c, HHG_EINVAL, "the context's device must be the current device");
     LevelDev<double>& v = view<double>(c, l);
-    const int np = residual_partials(c, v), most = (v.n >= SPLIT_MIN_N ? 4 : 1) * v.nv_nat + (v.nif + TPB - 1) / TPB;
-    if ((size_t)most > NOALLOC_MAX_PARTIALS)
+    const int np = residual_partials(c, v);
+    if ((size_t)np > NOALLOC_SCRATCH_DOUBLES)
         return fail(c, HHG_EINVAL,
-                    "level too large for the static scratch: " + std::to_string(most) +
-                        " partial sums, at most " + std::to_string(NOALLOC_MAX_PARTIALS));
+                    "level too large for the static scratch: " + std::to_string(np) +
+                        " partial sums, at most " + std::to_string(NOALLOC_SCRATCH_DOUBLES));
     hipStream_t s = (hipStream_t)stream;
     // every partial in [0, np) is written by its block before the sum reads
     // it, so the scratch needs no clearing between calls
@@ -3734,6 +3734,8 @@ bool check_level(const hhg_ctx* c, int l, std::string* err) {
     // grids fit the reduction buffers
     CK(full_blocks((int)h.vtiles.size()) + (h.nif + TPB - 1) / TPB <= c->npartials, "partials too small");
     CK((int)h.ctiles.size() <= c->npartials, "gradient partials too small");
+    CK(n >= SPLIT_MIN_N || (size_t)full_blocks((int)h.vtiles.size()) + (h.nif + TPB - 1) / TPB <= NOALLOC_SCRATCH_DOUBLES,
+       "static scratch too small");
     return true;
 }
 // The work vectors of the solvers: every one that a path of this context takes
