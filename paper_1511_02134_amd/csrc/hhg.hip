@@ -295,10 +295,14 @@ Lat<T> lat_geometry(const hhg_ctx* c, int l) {
 }
 
 // The workspace holds the lattice path's tables and vectors for Kuhn macros
-// without free-slip faces and at least one smoothed level.  The limits are
-// those of its 32-bit addresses and of lat_div.
-bool lat_reserved(const hhg_ctx* c) {
-    if (c->mi.general || c->mi.slip || c->L < 1) return false;
+// without free-slip faces and at least one smoothed level (whatever the form and
+// order, so that these options do not change its size).
+bool lat_reserved(const hhg_ctx* c) { return !c->mi.general && !c->mi.slip && c->L >= 1; }
+
+// The limits of its 32-bit addresses and of lat_div.  A level's slots in the
+// per-macro layout are at least its entries here and below 2^29, and with that and
+// the level-0 solver's limit every box of cells that is accepted keeps them all.
+bool lat_fits(const hhg_ctx* c) {
     const HostLevel& h = c->H[c->L];
     const int64_t lim = 1 << 21, plane = (int64_t)h.lat[0] * h.lat[1];
     const Lat<double> G = lat_geometry<double>(c, c->L);
@@ -381,6 +385,7 @@ hhg_status build_host(hhg_ctx* c, const hhg_mesh* mesh, int R, const hhg_opts* o
     }
     if (!build_coarse_for(c, &err)) return fail(c, HHG_EINVAL, err);
     c->lat = lat_applies(c);
+    if (c->lat && !lat_fits(c)) return fail(c, HHG_EINVAL, "internal error: level beyond the lattice's limits");
     return HHG_OK;
 }
 
@@ -1621,18 +1626,15 @@ void colour_pass_rb(hhg_ctx* c, int l, int p, bool vel, T* x, const T* rhs, hipS
 // red, black, red (a second black sweep right after the first would
 // recompute identical values), its first red half inside the pass that forms
 // f - B^T p; the pressure red (inside the pass that forms B u - g), black,
-// and with p_sweep = 1 black, red again
-// (vr: f - B^T p of this x is given, and the first red half is a sweep of
-// its own)
+// and with p_sweep = 1 black, red again.  hhg_smooth alone comes here: the cycles
+// of this order run on the lattice
 template <typename T>
-void uzawa_step_rb(hhg_ctx* c, int l, T* x, const T* b, T* t, hipStream_t s, const T* vr) {
-    if (!vr) full_pass_fused<T, MODE_RU>(c, l, x, b, t, 4, s);
+void uzawa_step_rb(hhg_ctx* c, int l, T* x, const T* b, T* t, hipStream_t s) {
+    full_pass_fused<T, MODE_RU>(c, l, x, b, t, 4, s);
     {
         TimedGroup tg(c, HHG_K_VEL, s, l == c->L);
-        const T* rhs = vr ? vr : t;
-        if (vr) colour_pass_rb<T>(c, l, 0, true, x, rhs, s);
-        colour_pass_rb<T>(c, l, 1, true, x, rhs, s);
-        colour_pass_rb<T>(c, l, 0, true, x, rhs, s);
+        colour_pass_rb<T>(c, l, 1, true, x, t, s);
+        colour_pass_rb<T>(c, l, 0, true, x, t, s);
     }
     full_pass_fused<T, MODE_BP>(c, l, x, b, t, c->opts.p_sweep == 1 ? 4 : 4 + 8, s);
     colour_pass_rb<T>(c, l, 1, false, x, t, s);
@@ -1642,10 +1644,10 @@ void uzawa_step_rb(hhg_ctx* c, int l, T* x, const T* b, T* t, hipStream_t s, con
     }
 }
 
-// one inexact Uzawa step (eq. Uzawa_smooth) in place.  vr (colour and
-// red-black orders): the velocity fields of vr hold f - B^T p of this x (b
-// itself when x = 0, or what the residual before the step wrote), so the step
-// skips the pass that forms it and starts with the velocity sweeps
+// one inexact Uzawa step (eq. Uzawa_smooth) in place.  vr (colour order): the
+// velocity fields of vr hold f - B^T p of this x (b itself when x = 0, or what
+// the residual before the step wrote), so the step skips the pass that forms it
+// and starts with the velocity sweeps
 template <typename T>
 void uzawa_step(hhg_ctx* c, int l, T* x, const T* b, T* t, hipStream_t s,
                 const T* vr = nullptr) {
@@ -1653,10 +1655,11 @@ void uzawa_step(hhg_ctx* c, int l, T* x, const T* b, T* t, hipStream_t s,
         uzawa_step_hybrid<T>(c, l, x, b, t, s);
         return;
     }
-    if (c->opts.ordering == 2) {
-        uzawa_step_rb<T>(c, l, x, b, t, s, vr);
-        return;
-    }
+    if constexpr (std::is_same_v<T, double>)
+        if (c->opts.ordering == 2) {
+            uzawa_step_rb<T>(c, l, x, b, t, s);
+            return;
+        }
     // symmetric Gauss-Seidel on A: colours 0 1 2 3 2 1 0 (a second sweep of
     // colour 3 right after the first would recompute identical values); the
     // first sweep runs inside the pass that forms f - B^T p, except for the D
@@ -2883,7 +2886,7 @@ hhg_status hhg_solve(hhg_ctx* c, void* xv, const void* bv, double rtol, int32_t 
     double* r = c->A[c->L].r64;
     // FP64 cycles smooth x itself: take its mirror once; the cycles and the
     // projection keep it current, so the stopping test may use it too.  On
-    // Kuhn macros in the Laplace form (colour or red-black order) the
+    // Kuhn macros with free-slip faces (Laplace form, colour order) the
     // stopping test also leaves f - B^T p of x in t for the next cycle's
     // first Uzawa step.
     const bool fp64 = c->opts.precision != 1;
