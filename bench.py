@@ -538,9 +538,12 @@ def main():
         raise RuntimeError("no finest-level velocity sweep was timed")
     vs = 8.0 if precision == 0 else 4.0
     # the cycles of the Laplace form in the colour and red-black orders run on
-    # the structured lattice; blocks of 2 x 2 rows from 8 M vertices on
+    # the structured lattice; blocks of 2 x 2 rows where one viscosity gives
+    # eight workgroups of 256 blocks for each of the 256 CUs
     lattice = not dform and ordering in (0, 2)
-    lat_vel = ("k_lat_vel_blk" if ordering == 2 and nvert >= 8.4e6 and float(nu.max()) == float(nu.min())
+    nx, ny, nz = (int(e) * (1 << cfg.R) + 1 for e in np.rint(xyz.max(axis=0)))
+    blocks = ny // 2 * ((nx - 1) // 4) // 256 * (nz // 2) >= 2048
+    lat_vel = ("k_lat_vel_blk" if ordering == 2 and blocks and float(nu.max()) == float(nu.min())
                else "k_lat_vel")
     # algorithmic bytes of one colour launch: one direction of the velocity
     # Gauss-Seidel reads u (3 values), f (3) and p and writes u (3) per finest

@@ -187,10 +187,14 @@ typedef struct {
                               eq. op_count); a colour sweep counts a quarter of its
                               operator, B and B^T count as B, the exact level-0
                               solves count nothing; the first Uzawa step of a level
-                              in a cycle counts no B when f - B^T p is given (b on
-                              levels whose iterate starts at 0; in the FP64 solve
-                              on Kuhn macros in the Laplace form, the stopping
-                              test's residual leaves it for the top level) */
+                              in a cycle counts no B when f - B^T p is b (levels
+                              whose iterate starts at 0) or part of the stopping
+                              test's residual (top level of the FP64 solve, Kuhn
+                              macros in the Laplace form).  These are the counts of
+                              the method: cycles on the lattice (see graphs) form
+                              the rows of B^T p in each velocity sweep, 1.5 times a
+                              step in the red-black order and 1.75 in the colours,
+                              and count them once, or not at all in those steps */
     /* Phase times of hhg_solve in ms, summed over all cycles and levels, from
      * hipEvent pairs on the stream; 0 unless hhg_set_phase_timing(ctx, 1)
      * (the events cost a few microseconds each and disable graph replay):

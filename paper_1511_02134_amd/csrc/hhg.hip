@@ -100,8 +100,9 @@ struct DevLevelArrays {
 };
 
 // Lattice path (lattice.hpp) of one level: device tables and work vectors
-// (4 fields each; the FP64 ones below the finest level only without mixed
-// precision, whose cycles run in FP32)
+// (4 fields each, in the memory of the per-macro ones as far as they fit; the
+// FP64 ones below the finest level only without mixed precision, whose cycles
+// run in FP32)
 struct LatLevel {
     int* rid = nullptr;
     unsigned char* rdir = nullptr;
@@ -257,11 +258,11 @@ bool opts_ok(const hhg_opts* o, std::string* err) {
     return true;
 }
 
-// The full passes over velocity rows run the point-block kernels, which read
-// every tap of the coupled blocks: the D form, and general meshes (whose a_1
-// stencils couple all 14 neighbours; their records hold the blocks
-// delta_kl A).  The colour sweeps of general meshes with a_1 read the 15
-// taps of A per component instead.
+// Velocity rows that couple all 14 neighbours: the D form, and general meshes.
+// The velocity cycles' residual runs the point-block kernel there, which reads
+// every tap of the coupled blocks (the records of general meshes with a_1 hold
+// the blocks delta_kl A).  K x, the residual and the colour sweeps of general
+// meshes with a_1 read the 15 taps of A per component instead.
 inline bool dpath(const hhg_ctx* c) { return c->opts.op == 1 || c->mi.general; }
 
 // level-0 system of the context's options: the solution operator for the
@@ -697,6 +698,7 @@ LatTables lat_tables(const hhg_ctx* c, int l) {
 }
 
 // The lattice path's tables, once at creation.
+hhg_status lat_visit_setup(hhg_ctx* c);
 hhg_status upload_lattice_tables(hhg_ctx* c) {
     if (!c->lat) return HHG_OK;
     hhg_status s;
@@ -736,18 +738,15 @@ hhg_status upload_lattice_tables(hhg_ctx* c) {
         const std::vector<double> zero(G.len, 0.0);
         if ((s = upload<double>(c, c->lat_pinv, zero.data(), zero.size())) != HHG_OK) return s;
     }
-    return HHG_OK;
+    return lat_visit_setup(c);
 }
 
 // Its records and constants, with every change of viscosity.
-hhg_status lat_visit_setup(hhg_ctx* c);
 hhg_status upload_lattice(hhg_ctx* c) {
     if (!c->lat) return HHG_OK;
     int kind = 0;
     for (const MacroInfo& m : c->mi.macros)
         if (m.nu != c->mi.macros[0].nu) kind = 1;
-    // attributes of the visits' kernels: per kind
-    const bool setup = c->G64.empty() || kind != c->lat_kind;
     c->lat_kind = kind;
     c->G64.assign(c->L + 1, Lat<double>{});
     c->G32.assign(c->L + 1, Lat<float>{});
@@ -830,7 +829,7 @@ hhg_status upload_lattice(hhg_ctx* c) {
         const std::vector<float> r32(recs.begin(), recs.end());
         if ((s = upload<float>(c, c->lat_rec32, r32.data(), r32.size())) != HHG_OK) return s;
     }
-    return setup ? lat_visit_setup(c) : HHG_OK;
+    return HHG_OK;
 }
 
 hhg_status upload_stencils(hhg_ctx* c) {
@@ -1967,8 +1966,13 @@ typedef LdsGeom<17, 17> Lds17;
 typedef LdsGeom<33, 9> Lds33;
 typedef LdsGeom<33, 17> Lds33w;
 
-// How one workgroup visits the level in values of `size` bytes (LatLevel),
-// 0 if its iterate does not fit the LDS or its lanes do not reach
+// How one workgroup visits the level in values of `size` bytes (LatLevel), 0 if it
+// does not.  The strides of the LDS layout are constants (a tap is an immediate
+// offset), and three are built: boxes of up to 17 x 17 vertices in x and y, 33 x 9,
+// and in FP32 33 x 17, as far as the iterate fits the LDS and the lanes reach.
+// Other boxes that would fit (long in y, or 41 x 9 x 9) run sweep by sweep: the
+// colour-order solve of 1 x 4 x 1 cells at 3 refinements takes 3.8 ms, that of
+// 4 x 1 x 1 2.2 ms.
 template <typename GEO>
 int lat_visit_geo(const Lat<double>& G, size_t size, size_t lds, int quads, int rim) {
     const GEO g{G.nx, G.ny, G.nz};
@@ -2020,8 +2024,8 @@ hipError_t lat_visit_any(hhg_ctx* c, int l, int lanes, const T* b, T* x, T* r, i
 #undef LAT_VISIT
 }
 
-// which levels are visited by one workgroup (with every change of viscosity:
-// the kind of the kernels may change)
+// which levels are visited by one workgroup, and the LDS limit of the kernels that
+// do it, of either kind (a later viscosity may change it)
 hhg_status lat_visit_setup(hhg_ctx* c) {
     int dev = 0, lds = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -2038,12 +2042,15 @@ hhg_status lat_visit_setup(hhg_ctx* c) {
         // take 42 us, its step 30
         if (g.visit64 > 1 && c->opts.ordering == 2) g.visit64 = 0;
         g.visit32 = c->opts.precision == 1 ? lat_visit_lanes(G, 4, c->lat_lds) : 0;
-        if (g.visit64)
-            HIPCHECK(c, lat_visit_any<double>(c, l, g.visit64, nullptr, nullptr, nullptr, 0, false, false, LatProg{},
-                                              nullptr, true));
-        if (g.visit32)
-            HIPCHECK(c, lat_visit_any<float>(c, l, g.visit32, nullptr, nullptr, nullptr, 0, false, false, LatProg{},
-                                             nullptr, true));
+        for (int kind = 0; kind < 2; ++kind) {
+            c->lat_kind = kind;
+            if (g.visit64)
+                HIPCHECK(c, lat_visit_any<double>(c, l, g.visit64, nullptr, nullptr, nullptr, 0, false, false,
+                                                  LatProg{}, nullptr, true));
+            if (g.visit32)
+                HIPCHECK(c, lat_visit_any<float>(c, l, g.visit32, nullptr, nullptr, nullptr, 0, false, false,
+                                                 LatProg{}, nullptr, true));
+        }
     }
     return HHG_OK;
 }
