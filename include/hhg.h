@@ -178,9 +178,10 @@ typedef struct {
     double rel_res;        /* r_final / r0 */
     double rho_mean;       /* (r_final / r0)^(1/cycles) */
     double rho_max;        /* largest ||r_k|| / ||r_{k-1}|| */
-    double t_solve_ms;     /* wall time of the cycles and of converting x and b to the
-                              layout they work in and x back, hipEvent timed on the
-                              stream (the first residual is not in it) */
+    double t_solve_ms;     /* wall time of the cycles, hipEvent timed on the stream;
+                              where they run on the lattice (see graphs) also that of
+                              converting x and b, of the first residual and of
+                              converting x back */
     double res_hist[256];  /* ||r_k||_2, k = 0..min(cycles, 255) */
     double n_op[4];        /* operator evaluations of A, B, C and M during the call,
                               weighted by level, sum_l 8^(l-L) n_op,l (Section 4.2,
@@ -203,7 +204,8 @@ typedef struct {
      *   coarse    the level-0 solve (with its residual and correction);
      *   residual  the residual before each restriction and the stopping test.
      * t_solve_ms minus their sum is the rest (projection, mixed-precision
-     * scaling, conversions of x and b, event gaps). */
+     * scaling, on the lattice the conversions and the first residual, event
+     * gaps). */
     double t_smooth_ms, t_transfer_ms, t_coarse_ms, t_residual_ms;
     /* The same event pairs by level (entries 0..L; the rest 0): level l's
      * smoothing, its residual, the restriction from it and the prolongation
